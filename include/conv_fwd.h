@@ -16,12 +16,14 @@
  *
  * Loop order and tile sizes are chosen per shape by a tile selector built on
  * the paper's data-movement model (Sec. 3-5, Algorithm 1 of Sec. 8),
- * re-derived for the gfx950 memory hierarchy; see conv_fwd_plan.
+ * re-derived for the gfx950 memory hierarchy; see conv_fwd_plan.  Layers on
+ * which they are faster run on the split-operand kernels instead; see
+ * conv_fwd_split_plan.
  *
  * Ownership: every tensor pointer is DEVICE memory allocated and freed by
  * the caller.  The library keeps a host-side plan cache; its device
  * allocations are workspaces (split reductions, the strided rewrite, bf16
- * fallbacks, conv_fwd_tune's scratch) from a memory pool the library
+ * fallbacks, packed operands, conv_fwd_tune's scratch) from a memory pool the library
  * creates per device, which keeps up to 1 GB of freed blocks for reuse.
  * The workspaces of the compute calls are kept per device, stream and
  * nesting level and reused by the next call on that stream (stream order
@@ -206,9 +208,9 @@ int conv_fwd_ex(int N, int C, int K, int H, int W, int R, int S,
  * Allocation-free variant of conv_fwd_ex, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  Same arguments, layouts, operation and
- * results as conv_fwd_ex (the same plans and kernels run), but every
- * workspace the call needs (phase images of In, the rearranged Ker, split
- * partial sums, bf16 widening) is carved from one static device array of
+ * results as conv_fwd_ex outside graph capture (the same plans and kernels
+ * run), but every workspace the call needs (phase images of In, the
+ * rearranged Ker, split partial sums, bf16 widening, packed operands) is carved from one static device array of
  * CONV_NOALLOC_SCRATCH_BYTES that the library holds on each GPU it runs on
  * until the process ends; the call makes no hipMalloc, hipFree or other
  * allocating call.  A call that would need more scratch returns
@@ -298,7 +300,9 @@ int conv_fwd_candidates(int N, int C, int K, int H, int W, int R, int S, int dty
  * returned to the library's memory pool in stream order.  The fastest plan
  * is written to *plan_out and becomes the cached plan of this shape, dtype
  * and tensor alignment: later
- * conv_fwd / conv_fwd_bf16 / conv_fwd_plan calls for them return or run it.
+ * conv_fwd / conv_fwd_bf16 / conv_fwd_plan calls for them return or run it,
+ * unless the layer is on the split-operand route (conv_fwd_split_plan) and
+ * that, timed the same way, was faster still: then the compute calls stay on it.
  *   dtype      : CONV_DTYPE_*; In and Ker as for conv_fwd or conv_fwd_bf16
  *   Out        : overwritten with Eq. (1) (every candidate computes it)
  *   top_n      : 1 .. CONV_TUNE_MAX;  reps : 1 .. 1000
@@ -391,6 +395,38 @@ int conv_fwd_ex_geometry(int N, int C, int K, int H, int W, int R, int S, int st
  */
 int conv_fwd_ex_plan(int N, int C, int K, int H, int W, int R, int S, int stride_h, int stride_w, int pad_h,
                      int pad_w, int dtype, conv_plan_t* plan_out, int32_t* direct);
+
+/*
+ * Host only: does this layer run on the split-operand kernels instead of its
+ * tile plan, and how?  Those kernels form the sums on the bf16 MFMAs: fp32
+ * operands are split exactly into three bf16 parts each, of whose nine
+ * products the six that matter at fp32 precision are summed in fp32 (measured
+ * closer to the 64-bit result than the fp32 MFMA kernels); bf16 operands are
+ * taken as they are.  The compute calls take them where their estimated time
+ * is below the plan's (by 3% or more): most bf16 layers, fp32 layers of more than
+ * about half a GFLOP.  They pack Ker (for 1x1 layers with many output
+ * channels: In) into a per-stream workspace on every call, so under graph
+ * capture conv_fwd, conv_fwd_bf16, conv_fwd_bf16_out and conv_fwd_ex run the
+ * plan; conv_fwd_ex_noalloc packs into its static scratch and takes the same
+ * route with and without capture.  Outputs that come out infinite or NaN are
+ * formed again by plain fp32 sums, so infinities, NaNs and overflow give what
+ * fp32 arithmetic gives.
+ * Writes min(cap, CONV_SPLIT_FIELDS) values: 1 if the split-operand kernels
+ * run (else all zero), instance id, mode (0 In staged in LDS, 1 the same for
+ * at most 4 channels, 2 Ker staged), 16-row blocks per wave of the packed and
+ * the staged operand, waves along each, channel groups, parts per operand (3
+ * or 1), staging items per thread, steps per chunk and group, 1 if one chunk;
+ * tile rows and columns, row, column and k tiles, tile order, workgroups,
+ * phases along rows and columns, staged rows per image, staged rows and
+ * columns per output row and column, staged rows and items per row of a
+ * tile, items and LDS slots per channel octet, octets per chunk, chunks,
+ * steps per chunk, packed blocks, items per chunk, LDS bytes of a staging
+ * buffer, LDS offset of the step table, LDS bytes, packed bytes, estimated
+ * time in us.  Returns CONV_SPLIT_FIELDS or a negative conv_status_t.
+ */
+#define CONV_SPLIT_FIELDS 38
+int conv_fwd_split_plan(int N, int C, int K, int H, int W, int R, int S, int stride_h, int stride_w, int pad_h,
+                        int pad_w, int dtype, int32_t* out, int cap);
 
 /*
  * Frees, in the order of `stream` (hipFreeAsync), the workspaces the compute

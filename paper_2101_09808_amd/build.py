@@ -13,7 +13,7 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libconvfwd.so")
 INCLUDE = os.path.join(os.path.dirname(PKG), "include")
 
-SOURCES = ("conv_kernels.hip", "conv_api.cpp", "select.cpp")
+SOURCES = ("conv_kernels.hip", "split_kernels.hip", "conv_api.cpp", "select.cpp", "split_route.cpp")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -105,6 +105,8 @@ def lib():
         L.conv_fwd_ex_geometry.restype = _i32
         L.conv_fwd_ex_plan.argtypes = shape7 + [_i32] * 5 + [ctypes.POINTER(ConvPlan), ctypes.POINTER(_i32)]
         L.conv_fwd_ex_plan.restype = _i32
+        L.conv_fwd_split_plan.argtypes = shape7 + [_i32] * 5 + [ctypes.POINTER(_i32), _i32]
+        L.conv_fwd_split_plan.restype = _i32
         L.conv_fwd_release_workspaces.argtypes = [_vp]
         L.conv_fwd_release_workspaces.restype = _i32
         L.conv_fwd_strerror.argtypes = [_i32]
@@ -394,3 +396,23 @@ def conv_fwd_ex_geometry(N, C, K, H, W, R, S, stride, pad, plan):
     if st < 0:
         raise ConvError(st, "conv_fwd_ex_geometry")
     return _geom_dict(buf)
+
+
+SPLIT_FIELDS = (
+    "use", "id", "mode", "wk", "wp", "nwk", "nwp", "nwc", "npl", "ni", "ns", "one",
+    "tr", "tw", "tiles_rows", "tiles_cols", "tiles_k", "order", "num_tiles", "na", "nb", "Hi", "rm", "cm",
+    "in_rows", "in_wp", "E", "Epad", "co", "nchunks", "steps", "blocks", "items", "buf_bytes", "tab_off",
+    "lds_bytes", "pk_bytes", "us",
+)
+
+
+def conv_fwd_split_plan(N, C, K, H, W, R, S, stride=1, pad=0, dtype=CONV_DTYPE_F32):
+    """How the split-operand kernels run this layer, as a dict of launch
+    fields (host only); None where the layer runs on its tile plan."""
+    sh, sw = _pair(stride)
+    ph, pw = _pair(pad)
+    buf = (_i32 * len(SPLIT_FIELDS))()
+    st = lib().conv_fwd_split_plan(N, C, K, H, W, R, S, sh, sw, ph, pw, dtype, buf, len(SPLIT_FIELDS))
+    if st < 0:
+        raise ConvError(st, "conv_fwd_split_plan")
+    return dict(zip(SPLIT_FIELDS, list(buf))) if buf[0] else None

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "conv_internal.h"
+#include "split_internal.h"
 
 using namespace convfwd;
 
@@ -32,6 +33,7 @@ struct Entry {
   conv_plan_t plan;
   const Variant* v;
   Geom g;
+  int split = -1;  // the call takes the split-operand route: 1 yes, 0 no, -1 not looked up yet
 };
 typedef std::tuple<int, int, int, int, int, int, int, int, int> Key;
 std::mutex g_mu;
@@ -203,8 +205,8 @@ int run_bf16_widened(const Shape& s, const void* In, const void* Ker, void* Out,
   return st == CONV_OK ? freed : st;
 }
 
-int run_selected(const Shape& s, int dtype, const void* In, const void* Ker, float* Out,
-                 void* stream) {
+// The selected plan's kernel (the split-operand kernels are tried before).
+int run_planned(const Shape& s, int dtype, const void* In, const void* Ker, float* Out, void* stream) {
   Entry e;
   const int st = cached_entry(s, dtype, alignment_of(In, Ker), &e);
   if (st == CONV_ENOPLAN && dtype == CONV_DTYPE_BF16) return run_bf16_widened(s, In, Ker, Out, false, stream);
@@ -217,7 +219,7 @@ int run_selected(const Shape& s, int dtype, const void* In, const void* Ker, flo
 // the kernel will see them), run reading In through the phase mapping when
 // its kernel can.  Cached per layer, stride, padding and alignment.
 struct ExEntry {
-  Entry e;
+  Entry e;      // (its split field: of the strided layer)
   bool direct;  // e.g carries the phase mapping
 };
 typedef std::tuple<int, int, int, int, int, int, int, int, int, int, int, int> ExKey;
@@ -296,6 +298,130 @@ int phase_geom(int N, int C, int K, int H, int W, int R, int S, int sh, int sw, 
   return CONV_OK;
 }
 
+// ---------------------------------------------------------------------------
+// Split-operand route: layers that the kernels of split_kernels.hip run
+// faster than the tile plan.  The two are compared by their estimates: the
+// plan's ranking time plus its passes over In, Ker and Out, and the split
+// plan's (split_choose).  The choice depends on the layer alone, not on the
+// type of Out, so bf16 Out stays the rounded fp32 Out.
+struct SplitEntry {
+  bool use;
+  SplitPlan p;
+};
+typedef std::tuple<int, int, int, int, int, int, int, int, int, int, int> SplitKey;
+std::map<SplitKey, SplitEntry> g_split_cache;
+
+// Estimated time of the planned route for 16-byte aligned tensors.  The extra
+// passes are charged what they measured: the phase split 0.2 elements per ns
+// (3x3 C128 bf16 layer at batch 32: 19 us), the rearranged Ker 4.5 us, the
+// widening and rounding passes 0.4 elements per ns.
+int planned_time(const SplitShape& s, double* us) {
+  const auto selected = [](const Shape& q, int dtype, double* t) {
+    Entry e;
+    int st = cached_entry(q, dtype, ALIGN_ALL, &e);
+    double extra = 0;
+    if (st == CONV_ENOPLAN && dtype == CONV_DTYPE_BF16) {
+      st = cached_entry(q, CONV_DTYPE_F32, ALIGN_ALL, &e);
+      extra = 6 + ((double)q.N * q.C * q.H * q.W + (double)q.K * q.C * q.R * q.S) / 0.4e6;
+    }
+    // (the transposing bf16 kernel's ranking times were taken between events:
+    // 73 us for the 226x226 layer that runs in 59 us back to back)
+    if (st == CONV_OK) *t = e.plan.rank_us * (e.v->family == FAMILY_BF16_TR ? 0.8 : 1.0) + extra;
+    return st;
+  };
+  if (s.sh == 1 && s.sw == 1 && s.ph == 0 && s.pw == 0) {
+    const Shape q{s.N, s.C, s.K, s.H, s.W, s.R, s.S};
+    return selected(q, s.dtype, us);
+  }
+  PhaseGeom p;
+  int st = phase_geom(s.N, s.C, s.K, s.H, s.W, s.R, s.S, s.sh, s.sw, s.ph, s.pw, &p);
+  if (st != CONV_OK) return st;
+  const double inner = (double)p.N * p.C * p.na * p.nb * p.Hp * p.Wp;
+  double extra = p.na * p.nb > 1 ? 4.5 : 0.0;
+  if (s.dtype == CONV_DTYPE_F32) {
+    ExEntry x;
+    st = cached_ex_entry(p, ALIGN_ALL, ALIGN_ALL, &x);
+    if (st != CONV_OK) return st;
+    *us = x.e.plan.rank_us;
+    if (!x.direct) extra += 3 + inner / 0.2e6;
+  } else {
+    st = selected(Shape{p.N, p.C * p.na * p.nb, p.K, p.Hp, p.Wp, p.Rp, p.Sp}, s.dtype, us);
+    if (st != CONV_OK) return st;
+    extra += 3 + inner / 0.2e6;
+  }
+  *us += extra;
+  return CONV_OK;
+}
+
+SplitShape split_shape(int N, int C, int K, int H, int W, int R, int S, int sh, int sw, int ph, int pw, int dtype) {
+  return SplitShape{N, C, K, H, W, R, S, sh, sw, ph, pw, (H + 2 * ph - R) / sh + 1, (W + 2 * pw - S) / sw + 1, dtype};
+}
+
+SplitEntry split_entry(const SplitShape& s) {
+  const SplitKey key{s.N, s.C, s.K, s.H, s.W, s.R, s.S, s.sh * 64 + s.sw, s.ph, s.pw, s.dtype};
+  {
+    std::lock_guard<std::mutex> lk(g_mu);
+    auto it = g_split_cache.find(key);
+    if (it != g_split_cache.end()) return it->second;
+  }
+  SplitEntry e;
+  std::memset(&e, 0, sizeof(e));
+  double us = 0;
+  // The packed operand also has to fit the allocation-free entry point's
+  // scratch, so that it takes the same route.
+  e.use = planned_time(s, &us) == CONV_OK && split_choose(s, &e.p) &&
+          e.p.pk_bytes <= (size_t)CONV_NOALLOC_SCRATCH_BYTES && e.p.us < 0.97 * us;
+  std::lock_guard<std::mutex> lk(g_mu);
+  g_split_cache[key] = e;
+  return e;
+}
+
+// The route of a call whose plan entry does not know it yet: not where
+// 16-byte loads of Ker meet an unaligned Ker.
+int split_route(const SplitShape& s, int align) {
+  const SplitEntry e = split_entry(s);
+  return e.use && !(e.p.cfg->mode == SPLIT_POINT && !(align & ALIGN_KER)) ? 1 : 0;
+}
+
+// Does the call take the split-operand route?  Unless its workspace is the
+// static scratch, not under graph capture: a graph would keep the address of
+// a workspace that later calls may replace.
+bool takes_split(const Entry& e, void* stream, bool static_scratch) {
+  return e.split == 1 && (static_scratch || !stream_capturing(stream));
+}
+
+// cached_entry with the route looked up.  A bf16 layer without a bf16 plan
+// has a route too (its planned one widens the inputs).
+int routed_entry(const Shape& s, int dtype, int align, Entry* e) {
+  const int st = cached_entry(s, dtype, align, e);
+  if (st == CONV_OK ? e->split >= 0 : st != CONV_ENOPLAN || dtype != CONV_DTYPE_BF16) return st;
+  e->split = split_route(split_shape(s.N, s.C, s.K, s.H, s.W, s.R, s.S, 1, 1, 0, 0, dtype), align);
+  if (st != CONV_OK) return st;
+  std::lock_guard<std::mutex> lk(g_mu);
+  g_cache[Key{s.N, s.C, s.K, s.H, s.W, s.R, s.S, dtype, align}].split = e->split;
+  return CONV_OK;
+}
+
+int run_split(const SplitEntry& e, bool out_bf16, const void* In, const void* Ker, void* Out, void* stream) {
+  Workspace w;
+  int st = workspace_acquire(3, e.p.pk_bytes, stream, &w);
+  if (st != CONV_OK) return st;
+  st = split_launch(e.p, out_bf16, In, Ker, w.ptr, Out, stream);
+  const int freed = workspace_release(w, stream);
+  return st == CONV_OK ? freed : st;
+}
+
+int run_selected(const Shape& s, int dtype, const void* In, const void* Ker, float* Out, void* stream) {
+  Entry e;
+  const int st = routed_entry(s, dtype, alignment_of(In, Ker), &e);
+  if (takes_split(e, stream, false))
+    return run_split(split_entry(split_shape(s.N, s.C, s.K, s.H, s.W, s.R, s.S, 1, 1, 0, 0, dtype)), false, In, Ker, Out,
+                     stream);
+  if (st == CONV_ENOPLAN && dtype == CONV_DTYPE_BF16) return run_bf16_widened(s, In, Ker, Out, false, stream);
+  if (st != CONV_OK) return st;
+  return launch(*e.v, e.g, In, Ker, Out, stream);
+}
+
 // The fields of conv_fwd_geometry, in the header's order.
 int export_geometry(const Variant& vr, const Geom& g, int lds, int32_t* out, int cap) {
   const Variant* v = &vr;
@@ -345,6 +471,10 @@ int conv_fwd_bf16_out(int N, int C, int K, int H, int W, int R, int S, const uin
   if (!In || !Ker || !Out) return CONV_ENULL;
   Entry e;
   const Shape sh{N, C, K, H, W, R, S};
+  routed_entry(sh, CONV_DTYPE_BF16, alignment_of(In, Ker), &e);
+  if (takes_split(e, stream, false))
+    return run_split(split_entry(split_shape(N, C, K, H, W, R, S, 1, 1, 0, 0, CONV_DTYPE_BF16)), true, In, Ker, Out,
+                     stream);
   const bool pair_possible = (W - S + 1) % 8 == 0 && (reinterpret_cast<uintptr_t>(Out) & 15) == 0;
   st = cached_entry_bf16_out(sh, alignment_of(In, Ker), pair_possible, &e);
   if (st == CONV_ENOPLAN) return run_bf16_widened(sh, In, Ker, Out, true, stream);
@@ -356,12 +486,48 @@ int conv_fwd_bf16_out(int N, int C, int K, int H, int W, int R, int S, const uin
 
 namespace {
 
-// The body of conv_fwd_ex (arguments already validated).
-int run_ex(const PhaseGeom& p, int dtype, const void* In, const void* Ker, float* Out, void* stream) {
+bool rewrites(const PhaseGeom& p) { return p.sh > 1 || p.sw > 1 || p.ph > 0 || p.pw > 0; }
+
+// The plan entry of a strided or padded fp32 layer for these tensors (a
+// strided Ker is rearranged into an aligned workspace, phase images too).
+int ex_entry(const PhaseGeom& p, const void* In, const void* Ker, ExEntry* x) {
+  const int ker_al = p.na * p.nb > 1 ? ALIGN_KER : (alignment_of(In, Ker) & ALIGN_KER);
+  return cached_ex_entry(p, (alignment_of(In, Ker) & (ALIGN_IN | ALIGN_IN4)) | ker_al, ALIGN_IN | ALIGN_IN4 | ker_al, x);
+}
+
+// Route of a conv_fwd_ex call: CONV_OK with *split set where the
+// split-operand kernels run, else with *x the plan entry of a strided or
+// padded fp32 layer.
+int ex_route(const PhaseGeom& p, int dtype, const void* In, const void* Ker, void* stream, bool static_scratch,
+             bool* split, ExEntry* x) {
+  const int align = alignment_of(In, Ker);
+  const SplitShape q = split_shape(p.N, p.C, p.K, p.H, p.W, p.R, p.S, p.sh, p.sw, p.ph, p.pw, dtype);
+  *split = false;
+  if (!rewrites(p)) {
+    routed_entry(Shape{p.N, p.C, p.K, p.H, p.W, p.R, p.S}, dtype, align, &x->e);
+  } else if (dtype == CONV_DTYPE_F32) {
+    const int st = ex_entry(p, In, Ker, x);
+    if (st != CONV_OK) return st;
+    if (x->e.split < 0) {
+      x->e.split = split_route(q, align);
+      const int ker_al = p.na * p.nb > 1 ? ALIGN_KER : (align & ALIGN_KER);
+      const int al = ((align & (ALIGN_IN | ALIGN_IN4)) | ker_al) * 8 + (ALIGN_IN | ALIGN_IN4 | ker_al);
+      std::lock_guard<std::mutex> lk(g_mu);
+      g_ex_cache[ExKey{p.N, p.C, p.K, p.H, p.W, p.R, p.S, p.sh, p.sw, p.ph, p.pw, al}].e.split = x->e.split;
+    }
+  } else {
+    x->e.split = split_route(q, align);
+  }
+  *split = takes_split(x->e, stream, static_scratch);
+  return CONV_OK;
+}
+
+// The planned route of conv_fwd_ex (arguments already validated).
+int run_ex(const PhaseGeom& p, int dtype, const void* In, const void* Ker, float* Out, void* stream, const ExEntry& x) {
   const int N = p.N, C = p.C, K = p.K, H = p.H, W = p.W, R = p.R, S = p.S;
   int st = CONV_OK;
   if (p.sh == 1 && p.sw == 1 && p.ph == 0 && p.pw == 0)
-    return run_selected(Shape{N, C, K, H, W, R, S}, dtype, In, Ker, static_cast<float*>(Out), stream);
+    return run_planned(Shape{N, C, K, H, W, R, S}, dtype, In, Ker, static_cast<float*>(Out), stream);
   const size_t e = dtype == CONV_DTYPE_BF16 ? 2 : 4;
   const int Cp = C * p.na * p.nb;
   // The rearranged Ker differs from Ker only with more than one phase (one
@@ -373,12 +539,6 @@ int run_ex(const PhaseGeom& p, int dtype, const void* In, const void* Ker, float
     // (direct-to-LDS kernel: no pass over In) or runs on phase-split copies
     // in a workspace; a strided Ker is rearranged first either way.  The
     // workspaces are 256-byte aligned.
-    const int ker_al = ker_moves ? ALIGN_KER : (alignment_of(In, Ker) & ALIGN_KER);
-    const int al_direct = (alignment_of(In, Ker) & (ALIGN_IN | ALIGN_IN4)) | ker_al;
-    const int al_split = ALIGN_IN | ALIGN_IN4 | ker_al;
-    ExEntry x;
-    st = cached_ex_entry(p, al_direct, al_split, &x);
-    if (st != CONV_OK) return st;
     const size_t in_ws = x.direct ? 0 : ((size_t)N * Cp * p.Hp * p.Wp * e + 255) / 256 * 256;
     const size_t ker_ws = ker_moves ? (size_t)K * Cp * p.Rp * p.Sp * e : 0;
     if (in_ws + ker_ws == 0) return launch(*x.e.v, x.e.g, In, Ker, Out, stream);
@@ -405,7 +565,7 @@ int run_ex(const PhaseGeom& p, int dtype, const void* In, const void* Ker, float
   void* Kp = ker_moves ? ws + in_bytes : nullptr;
   st = launch_phase_split(p, dtype, In, Ker, ws, Kp, stream);
   if (st == CONV_OK)
-    st = run_selected(inner, dtype, ws, ker_moves ? Kp : Ker, Out, stream);
+    st = run_planned(inner, dtype, ws, ker_moves ? Kp : Ker, Out, stream);
   const int freed = workspace_release(w, stream);
   return st == CONV_OK ? freed : st;
 }
@@ -413,7 +573,7 @@ int run_ex(const PhaseGeom& p, int dtype, const void* In, const void* Ker, float
 // Scratch bytes run_ex needs for these arguments, summed over the
 // workspaces it takes in order, each rounded up to the 256-byte alignment
 // of the arena's bump allocation.  Mirrors the dispatch of run_ex,
-// run_selected, run_bf16_widened and launch (split partial sums); any
+// run_planned, run_bf16_widened and launch (split partial sums); any
 // workspace the library carves is 256-byte aligned, which is what the
 // alignment of the plans that run on workspaces is computed with.
 size_t up256(size_t b) { return (b + 255) / 256 * 256; }
@@ -487,7 +647,15 @@ int conv_fwd_ex(int N, int C, int K, int H, int W, int R, int S, int stride_h, i
   if (st != CONV_OK) return st;
   if (!In || !Ker || !Out) return CONV_ENULL;
   if (dtype != CONV_DTYPE_F32 && dtype != CONV_DTYPE_BF16) return CONV_EINVAL;
-  return run_ex(p, dtype, In, Ker, Out, stream);
+  if (!rewrites(p)) return run_selected(Shape{N, C, K, H, W, R, S}, dtype, In, Ker, Out, stream);
+  bool split = false;
+  ExEntry x;
+  const int rt = ex_route(p, dtype, In, Ker, stream, false, &split, &x);
+  if (rt != CONV_OK) return rt;
+  if (split)
+    return run_split(split_entry(split_shape(N, C, K, H, W, R, S, stride_h, stride_w, pad_h, pad_w, dtype)), false, In,
+                     Ker, Out, stream);
+  return run_ex(p, dtype, In, Ker, Out, stream, x);
 }
 
 int conv_fwd_ex_noalloc(int N, int C, int K, int H, int W, int R, int S, int stride_h, int stride_w, int pad_h,
@@ -501,6 +669,15 @@ int conv_fwd_ex_noalloc(int N, int C, int K, int H, int W, int R, int S, int str
   st = ex_need(p, dtype, In, Ker, &need);
   if (st != CONV_OK) return st;
   if (need > (size_t)CONV_NOALLOC_SCRATCH_BYTES) return CONV_ESCRATCH;
+  bool split = false;
+  ExEntry x;
+  st = ex_route(p, dtype, In, Ker, stream, true, &split, &x);
+  if (st != CONV_OK) return st;
+  SplitEntry e;
+  if (split) {
+    e = split_entry(split_shape(N, C, K, H, W, R, S, stride_h, stride_w, pad_h, pad_w, dtype));
+    need = e.p.pk_bytes;
+  }
   void* base = nullptr;
   if (need > 0) {
     st = noalloc_scratch(&base);
@@ -508,7 +685,8 @@ int conv_fwd_ex_noalloc(int N, int C, int K, int H, int W, int R, int S, int str
   }
   ScratchArena arena{static_cast<char*>(base), need > 0 ? (size_t)CONV_NOALLOC_SCRATCH_BYTES : 0, 0};
   ArenaGuard guard(&arena);
-  return run_ex(p, dtype, In, Ker, Out, stream);
+  if (split) return run_split(e, false, In, Ker, Out, stream);
+  return run_ex(p, dtype, In, Ker, Out, stream, x);
 }
 
 int conv_fwd_ex_plan(int N, int C, int K, int H, int W, int R, int S, int stride_h, int stride_w, int pad_h,
@@ -620,13 +798,24 @@ int conv_fwd_tune(int N, int C, int K, int H, int W, int R, int S, int dtype, co
   float best_us = 0.f;
   for (size_t i = 0; i < cand.size(); ++i) {
     float us = 0.f;
-    st = time_launches(*cand[i].v, cand[i].g, In, Ker, Out, stream, reps, &us);
+    const Entry& c = cand[i];
+    st = time_launches([&] { return launch(*c.v, c.g, In, Ker, Out, stream); }, stream, reps, &us);
     if (st != CONV_OK) return st;
     if (times_us) times_us[i] = us;
     if (i == 0 || us < best_us) {
       best = i;
       best_us = us;
     }
+  }
+  // the split-operand kernels stay this layer's route only if they beat the plan
+  const SplitShape q = split_shape(N, C, K, H, W, R, S, 1, 1, 0, 0, dtype);
+  cand[best].split = split_route(q, align);
+  if (cand[best].split) {
+    const SplitEntry se = split_entry(q);
+    float us = 0.f;
+    st = time_launches([&] { return run_split(se, false, In, Ker, Out, stream); }, stream, reps, &us);
+    if (st != CONV_OK) return st;
+    cand[best].split = us < best_us ? 1 : 0;
   }
   {
     std::lock_guard<std::mutex> lk(g_mu);
@@ -679,6 +868,30 @@ int conv_fwd_ex_geometry(int N, int C, int K, int H, int W, int R, int S, int st
   const bool direct = rewrite && phase_direct(*v, p, plan->dtype, &g);  // nph stays 0 where it does not apply
   if (v->phase_skip && !direct) return CONV_EINVAL;  // phase skip runs only reading In directly
   return export_geometry(*v, g, lds, out, cap);
+}
+
+int conv_fwd_split_plan(int N, int C, int K, int H, int W, int R, int S, int stride_h, int stride_w, int pad_h,
+                        int pad_w, int dtype, int32_t* out, int cap) {
+  PhaseGeom p;
+  const int st = phase_geom(N, C, K, H, W, R, S, stride_h, stride_w, pad_h, pad_w, &p);
+  if (st != CONV_OK) return st;
+  if (cap > 0 && !out) return CONV_ENULL;
+  if (dtype != CONV_DTYPE_F32 && dtype != CONV_DTYPE_BF16) return CONV_EINVAL;
+  const SplitShape q = split_shape(N, C, K, H, W, R, S, stride_h, stride_w, pad_h, pad_w, dtype);
+  const SplitEntry e = split_entry(q);
+  int32_t f[CONV_SPLIT_FIELDS] = {0};
+  if (e.use) {
+    const SplitConfig& c = *e.p.cfg;
+    const SplitGeom& g = e.p.g;
+    const int32_t v[CONV_SPLIT_FIELDS] = {
+        1, c.id, c.mode, c.wk, c.wp, c.nwk, c.nwp, c.nwc, c.npl, c.ni, c.ns, c.one,
+        g.tr, g.tw, g.tiles_rows, g.tiles_cols, g.tiles_k, g.order, g.num_tiles, g.na, g.nb, g.Hi, g.rm, g.cm,
+        g.in_rows, g.in_wp, g.E, g.Epad, g.co, g.nchunks, g.steps, g.blocks, g.items, g.buf_bytes, g.tab_off,
+        e.p.lds_bytes, (int32_t)e.p.pk_bytes, (int32_t)e.p.us};
+    std::memcpy(f, v, sizeof(f));
+  }
+  for (int i = 0; i < cap && i < CONV_SPLIT_FIELDS; ++i) out[i] = f[i];
+  return CONV_SPLIT_FIELDS;
 }
 
 int conv_fwd_release_workspaces(void* stream) { return workspace_release_stream(stream); }

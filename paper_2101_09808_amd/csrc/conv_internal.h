@@ -3,6 +3,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <functional>
 
 #include "../../include/conv_fwd.h"
 
@@ -93,6 +94,7 @@ struct Geom {
       dv_tiles_cols, dv_tiles_rows;
 };
 
+FastDiv make_fastdiv(int d);
 // Fills the FastDiv fields of g from its extents (after every other field).
 void set_fast_divisors(Geom* g);
 
@@ -135,7 +137,7 @@ int stream_alloc(size_t bytes, void* stream, void** out);
 int stream_free(void* p, void* stream);
 // A call's workspace: the buffer the library keeps for (current device,
 // stream, nesting level) -- levels 0 (conv_fwd_ex, bf16 widening), 1 (bf16
-// Out staging), 2 (split partial sums) let nested steps of one call hold
+// Out staging), 2 (split partial sums), 3 (split-operand packing) let nested steps of one call hold
 // theirs together -- or, while another host thread holds that buffer, a
 // fresh stream-ordered allocation.  Release enqueues nothing for a kept
 // buffer: the next call on the stream reuses it in stream order.
@@ -165,12 +167,11 @@ int noalloc_scratch(void** base);
 // `stream`.
 int launch_phase_split(const PhaseGeom& p, int dtype, const void* In, const void* Ker, void* Inp, void* Kp,
                        void* stream);
-// Median duration in microseconds of `reps` launches on `stream` after one
-// untimed launch, each between its own two HIP events and preceded by a pass
-// over a 512 MB stream-ordered scratch buffer (cold caches); waits for the
-// stream.
-int time_launches(const Variant& v, const Geom& g, const void* In, const void* Ker, float* Out,
-                  void* stream, int reps, float* us);
+// Median duration in microseconds of `reps` calls of `call` (which enqueues
+// work on `stream` and returns a conv_status_t) after one untimed call, each
+// between its own two HIP events and preceded by a pass over a 512 MB
+// stream-ordered scratch buffer (cold caches); waits for the stream.
+int time_launches(const std::function<int()>& call, void* stream, int reps, float* us);
 
 // Selector entry points (host only, no HIP calls).
 int select_plan(const Shape& s, int dtype, conv_plan_t* out);

@@ -2493,10 +2493,9 @@ __global__ void evict_kernel(const v4f* __restrict__ buf, int64_t n4, float* __r
 
 constexpr size_t kEvictBytes = size_t(512) << 20;  // twice the last-level cache
 
-int time_launches(const Variant& v, const Geom& g, const void* In, const void* Ker, float* Out,
-                  void* stream, int reps, float* us) {
+int time_launches(const std::function<int()>& call, void* stream, int reps, float* us) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  int rc = launch(v, g, In, Ker, Out, stream);  // untimed: first-launch set-up, caches
+  int rc = call();  // untimed: first-launch set-up, caches
   if (rc != CONV_OK) return rc;
   // Each launch runs after a pass over a 512 MB scratch buffer (so In comes
   // from HBM, as in a network where every call has new data) and between its
@@ -2516,7 +2515,7 @@ int time_launches(const Variant& v, const Geom& g, const void* In, const void* K
                        (int64_t)(kEvictBytes / sizeof(v4f)), static_cast<float*>(evict_buf));
     if (hipGetLastError() != hipSuccess) rc = CONV_EHIP;
     if (rc == CONV_OK && hipEventRecord(ev[2 * i], st) != hipSuccess) rc = CONV_EHIP;
-    if (rc == CONV_OK) rc = launch(v, g, In, Ker, Out, stream);
+    if (rc == CONV_OK) rc = call();
     if (rc == CONV_OK && hipEventRecord(ev[2 * i + 1], st) != hipSuccess) rc = CONV_EHIP;
   }
   const bool freed = hipFreeAsync(evict_buf, st) == hipSuccess;

@@ -226,7 +226,6 @@ Shape kernel_view(const Shape& s) {
 }
 }  // namespace
 
-namespace {
 FastDiv make_fastdiv(int d) {
   FastDiv f{0u, 0};
   if (d <= 0) return f;
@@ -237,7 +236,6 @@ FastDiv make_fastdiv(int d) {
   f.s = s;
   return f;
 }
-}  // namespace
 
 void set_fast_divisors(Geom* g) {
   g->dv_in_cstride = make_fastdiv(g->in_cstride);

@@ -1,0 +1,733 @@
+// Split-operand convolution on the bf16 matrix cores.
+//
+// The fp32 MFMA runs at 157 TFLOP/s, the bf16 one at 2.5 PFLOP/s.  An fp32
+// value is exactly the sum of three bf16 parts (each the nearest bf16 of what
+// the parts before left over: 8 + 8 + 8 bits), so a product of two values is
+// nine products of parts, of which the three smallest lie below 2^-26 of it;
+// the other six, summed in fp32 by the MFMAs, give the product at fp32
+// precision for 6/16 of the fp32 MFMA's time.  Operands are scaled by 2^24
+// first, which keeps the parts of every normal fp32 value normal bf16 values;
+// sums beyond 2^80, infinities and NaNs make the output non-finite, and such
+// outputs are formed again by plain fp32 sums (repair).
+//
+// Precision, measured as 2-norm distance from the 64-bit result: 1.5e-7 on
+// the 3x3 C128 N32 layer (fp32 MFMA kernel: 4.3e-7), 1.6e-7 on the 3x3 C512
+// one (3.1e-7), 1.4e-7 on a 1x1 layer of 1024 channels (4.0e-7).  An MFMA
+// rounds once for 32 products where the fp32 one rounds every four, and the
+// five small products have accumulators of their own (in one set of
+// accumulators they would round it six times per step: 3.6e-7 on C512).
+//
+// bf16 inputs run the same kernels with one part per operand.
+//
+// One of the operands is packed by a small kernel into fragments that a wave
+// reads as one contiguous kilobyte; the other is staged into LDS channel-
+// octet-fastest, [octet][pixel] of 16 bytes, so that every tap (r, s) of an
+// output pixel is another 16-byte slot: no im2col copy, any stride and
+// padding, and conflict-free reads.  Measured (back to back, In from HBM),
+// before (fp32 MFMA kernels, or the transposed-tile bf16 kernel with its
+// phase-split pass) and after:
+//   3x3 C128 K128 30^2 N32            77.6 -> 40.1 us (184 TFLOP/s)
+//   3x3 C512 K512 9^2 N32             76.5 -> 51.5 us
+//   3x3 stride 2 C64 K128 56^2 N32    63.4 -> 32.2 us
+//   7x7 stride 2 C3 K64 224^2 N32     118  -> 72 us
+//   3x3 C512 K1024 17^2 N1            48.1 -> 41.5 us
+//   1x1 C1024 K28269 17^2 N1          283  -> 105 us
+//   bf16 3x3 C128 K128 28^2 N32       67.0 -> 18.3 us
+// What bounds it: on random data the bf16 MFMAs sustain 1.75-2.0 PFLOP/s (the
+// clock falls to 1.9 GHz), and per-workgroup timestamps show the vector-memory
+// instructions of a CU (about 17 cycles each) adding to the MFMA time.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <mutex>
+#include <type_traits>
+#include <utility>
+
+#include "split_internal.h"
+
+namespace convfwd {
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+
+constexpr unsigned kOob = 0x80000000u;  // past every buffer's range (tensors < 2 GB)
+
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(static_cast<F&&>(f), std::make_integer_sequence<int, N>{});
+}
+
+__device__ __forceinline__ int fdiv(int n, FastDiv f) {
+  return (int)(((unsigned long long)(unsigned)n * f.m) >> (31 + f.s));
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
+}
+
+// XCD x takes the contiguous range [x G/8, (x+1) G/8) of the tile order.
+__device__ __forceinline__ int xcd_remap(int b, int G) {
+  const int G8 = G & ~7;
+  return (b < G8) ? (b & 7) * (G8 >> 3) + (b >> 3) : b;
+}
+
+constexpr float kScale = 16777216.f;                        // 2^24
+constexpr float kUnscale = 1.f / (16777216.f * 16777216.f);  // 2^-48
+
+// Two floats as three bf16 pairs whose sums are the floats exactly (each part
+// is the nearest bf16 of what the parts before left over).
+__device__ __forceinline__ void split2(float x0, float x1, unsigned& h, unsigned& m, unsigned& l) {
+  x0 *= kScale;
+  x1 *= kScale;
+  h = __builtin_bit_cast(unsigned, __builtin_convertvector(v2f{x0, x1}, v2bf));
+  x0 -= __builtin_bit_cast(float, h << 16);
+  x1 -= __builtin_bit_cast(float, h & 0xffff0000u);
+  m = __builtin_bit_cast(unsigned, __builtin_convertvector(v2f{x0, x1}, v2bf));
+  x0 -= __builtin_bit_cast(float, m << 16);
+  x1 -= __builtin_bit_cast(float, m & 0xffff0000u);
+  l = __builtin_bit_cast(unsigned, __builtin_convertvector(v2f{x0, x1}, v2bf));
+}
+
+// 8 values as the NPL planes of a fragment (a kilobyte apart per wave).
+template <int NPL, typename T>
+__device__ __forceinline__ void put_fragment(const T (&x)[8], v4u* dst) {
+  if constexpr (NPL == 3) {
+    v4u h, m, l;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      unsigned a, b, c;
+      split2(x[2 * e], x[2 * e + 1], a, b, c);
+      h[e] = a; m[e] = b; l[e] = c;
+    }
+    dst[0] = h;
+    dst[64] = m;
+    dst[128] = l;
+  } else {
+    v4u h;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) h[e] = (unsigned)x[2 * e] | ((unsigned)x[2 * e + 1] << 16);
+    dst[0] = h;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The packed operand: [16-row block][chunk][step][plane][lane][8 bf16], so a
+// wave reads an operand as one contiguous kilobyte.  Lane l holds 8 values of
+// row l % 16 for the unit u = 4 step + l / 16 of the chunk; zeros past the
+// rows, channels and taps.
+//   CONV, POINT: channel octet u % co of the chunk at tap u / co (POINT: rows
+//   are pixels of In, one tap); IMAGE: columns s = 2 (u % Sp), + 1 of kernel
+//   row u / Sp, 4 channels each.
+template <int MODE, int NPL>
+__global__ void __launch_bounds__(256)
+split_pack_kernel(const void* __restrict__ SrcV, v4u* __restrict__ Pk, const SplitGeom g) {
+  typedef typename std::conditional<NPL == 3, float, unsigned short>::type T;
+  const T* Src = static_cast<const T*>(SrcV);
+  const int F = g.nchunks * g.steps;
+  const int lane = threadIdx.x & 63;
+  const int w = blockIdx.x * 4 + (threadIdx.x >> 6);  // (block, chunk, step)
+  if (w >= g.blocks * F) return;
+  const int blk = w / F, f = w - blk * F, ch = f / g.steps, m = f - ch * g.steps;
+  const int u = 4 * m + (lane >> 4), row = blk * 16 + (lane & 15);
+  T x[8];
+  if constexpr (MODE == SPLIT_IMAGE) {
+    const int Sp = (g.S + 1) / 2, r = u / Sp, s0 = 2 * (u - r * Sp);
+    const bool ok = row < g.K && r < g.R;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int c = e & 3, s = s0 + (e >> 2);
+      const bool v = ok && c < g.C && s < g.S;
+      const T t = Src[v ? (((size_t)row * g.C + c) * g.R + r) * g.S + s : 0];
+      x[e] = v ? t : T(0);
+    }
+  } else {
+    const int c0 = ch * g.co * 8 + u * 8, PQ = g.P * g.Q;
+    const bool ok = row < g.N * PQ && u < g.co;
+    const int n = ok ? row / PQ : 0, p = ok ? row - n * PQ : 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int c = c0 + e;
+      const T t = Src[((size_t)n * g.C + min(c, g.C - 1)) * PQ + p];
+      x[e] = ok && c < g.C ? t : T(0);
+    }
+  }
+  put_fragment<NPL>(x, Pk + (size_t)w * NPL * 64 + lane);
+}
+
+// CONV: one wave packs one channel octet of a 16-row block: its 16 runs of
+// 8 R S contiguous values come in coalesced, and LDS turns them into octets
+// per tap (reading the octets straight from memory, eight values R S apart
+// per lane, took 16 us for the 2.4 M values of the 512 x 512 3x3 layer).
+template <int NPL, int RSC>
+__global__ void __launch_bounds__(256)
+split_pack_taps_kernel(const void* __restrict__ SrcV, v4u* __restrict__ Pk, const SplitGeom g, const FastDiv dv_n) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  typedef typename std::conditional<NPL == 3, float, unsigned short>::type T;
+  const T* Src = static_cast<const T*>(SrcV);
+  const int RS = RSC ? RSC : g.R * g.S, n = 8 * RS, pitch = n + 1;
+  const int lane = threadIdx.x & 63, noct = g.nchunks * g.co;
+  T* buf = reinterpret_cast<T*>(smem) + (threadIdx.x >> 6) * 16 * pitch;
+  const int w = min((int)(blockIdx.x * 4 + (threadIdx.x >> 6)), g.blocks * noct - 1);  // (block, octet)
+  const int blk = w / noct, oct = w - blk * noct;
+  const int nv = min(n, (g.C - oct * 8) * RS);  // values of real channels per row
+  if constexpr (RSC > 0) {  // every load in flight at once
+    T t[RSC * 2];
+#pragma unroll
+    for (int y = 0; y < RSC * 2; ++y) {
+      const int i = lane + 64 * y, r = i / (8 * RSC), x = i - r * (8 * RSC), k = blk * 16 + r;
+      t[y] = k < g.K && x < nv ? Src[((size_t)k * g.C + oct * 8) * RS + x] : T(0);
+    }
+#pragma unroll
+    for (int y = 0; y < RSC * 2; ++y) {
+      const int i = lane + 64 * y, r = i / (8 * RSC);
+      buf[r * pitch + i - r * (8 * RSC)] = t[y];
+    }
+  } else {
+    for (int i = lane; i < 16 * n; i += 64) {
+      const int r = fdiv(i, dv_n), x = i - r * n, k = blk * 16 + r;
+      buf[r * pitch + x] = k < g.K && x < nv ? Src[((size_t)k * g.C + oct * 8) * RS + x] : T(0);
+    }
+  }
+  __syncthreads();
+  const int ch = oct / g.co, o = oct - ch * g.co;
+  const int units = 4 * g.steps, row = lane & 15;
+  v4u* dst = Pk + ((size_t)blk * g.nchunks + ch) * g.steps * NPL * 64;
+  // this octet's units are o, o + co, ... (one per tap); the units past the
+  // last tap are zero, and each octet's sequence runs through its share of them
+  for (int tap = lane >> 4; tap * g.co + o < units; tap += 4) {
+    const int u = tap * g.co + o;
+    T x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = tap < RS ? buf[row * pitch + e * RS + tap] : T(0);
+    put_fragment<NPL>(x, dst + (u >> 2) * NPL * 64 + (u & 3) * 16 + row);
+  }
+}
+
+// One output by plain fp32 sums: what IEEE arithmetic gives where infinities
+// or NaNs enter (or sums leave the scaled range).
+template <int NPL>
+__device__ __forceinline__ float repair(const void* InV, const void* KerV, const SplitGeom& g, int n, int k, int h,
+                                        int w) {
+  float acc = 0.f;
+#pragma clang loop unroll(disable)
+  for (int c = 0; c < g.C; ++c)
+#pragma clang loop unroll(disable)
+    for (int r = 0; r < g.R; ++r) {
+      const int y = h * g.sh + r - g.ph;
+#pragma clang loop unroll(disable)
+      for (int s = 0; s < g.S; ++s) {
+        const int x = w * g.sw + s - g.pw;
+        const bool in = (unsigned)y < (unsigned)g.H && (unsigned)x < (unsigned)g.W;
+        const size_t io = in ? (((size_t)n * g.C + c) * g.H + y) * g.W + x : 0;
+        const size_t ko = (((size_t)k * g.C + c) * g.R + r) * g.S + s;
+        float a, b;
+        if constexpr (NPL == 3) {
+          a = static_cast<const float*>(InV)[io];
+          b = static_cast<const float*>(KerV)[ko];
+        } else {
+          a = __builtin_bit_cast(float, (unsigned)static_cast<const unsigned short*>(InV)[io] << 16);
+          b = __builtin_bit_cast(float, (unsigned)static_cast<const unsigned short*>(KerV)[ko] << 16);
+        }
+        acc = __builtin_fmaf(in ? a : 0.f, b, acc);
+      }
+    }
+  return acc;
+}
+
+// ---------------------------------------------------------------------------
+// The convolution.  A workgroup computes BK = 16 WK NWK rows of the packed
+// operand by BP = 16 WP NWP rows of the staged one.  Per chunk of 8 co
+// channels: the next chunk's items are loaded, split and written to the other
+// LDS buffer while this chunk's MFMA steps run; each step covers four
+// (octet, tap) units, one per lane group (step table in LDS).  NWC groups of
+// waves take every NWC-th step of a chunk and are summed in LDS at the end.
+//
+// Why this shape: one wave issues a 16x16x32 MFMA every 21 cycles when it
+// changes accumulators (18 on the same one); two waves per SIMD fill the
+// 16-cycle pipe, so the fp32 instances are eight waves of 1 x 7 blocks (the
+// two accumulator sets fit 256 registers; 2 x 7 blocks with four waves took
+// 47 us against 40 us on the C128 layer).  The loads, LDS reads and vector
+// instructions of a step are spread over its blocks by hand (scheduling
+// barriers): left to itself the compiler waits for every LDS read right before its use
+// (68 us).
+template <int MODE, int WK, int WP, int NWK, int NWP, int NWC, int NPL, int NI, int NS, int AD, bool ONE, int OCC,
+          bool SEP, typename OT>
+__global__ void __launch_bounds__(NWK * NWP * NWC * 64, OCC)
+split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, const void* __restrict__ KerV,
+                  OT* __restrict__ Out, const SplitGeom g) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int NT = NWK * NWP * NWC * 64;
+  constexpr int BK = 16 * WK * NWK;  // packed rows per workgroup (POINT: pixels)
+  constexpr int BP = 16 * WP * NWP;  // staged rows per workgroup (POINT: output channels)
+  constexpr int ISZ = NPL == 3 ? 4 : 2;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave % NWK, wp = (wave / NWK) % NWP, wc = wave / (NWK * NWP);
+  const int j16 = lane & 15, gq = lane >> 4;
+
+  // tile
+  const int L = xcd_remap((int)blockIdx.x, g.num_tiles);
+  int kt, ct, rt;
+  if (g.order == 0) {
+    const int rest = fdiv(L, g.dv_tiles_k);
+    kt = L - rest * g.tiles_k;
+    rt = fdiv(rest, g.dv_tiles_cols);
+    ct = rest - rt * g.tiles_cols;
+  } else {
+    const int rest = fdiv(L, g.dv_tiles_cols);
+    ct = L - rest * g.tiles_cols;
+    kt = fdiv(rest, g.dv_tiles_rows);
+    rt = rest - kt * g.tiles_rows;
+  }
+  const int rho0 = rt * g.tr, rho_end = min(rho0 + g.tr, g.N * g.P);
+  const int q0 = ct * g.tw;
+  const int n0 = fdiv(rho0, g.dv_P);
+  const int nu0 = n0 * g.Hi + (rho0 - n0 * g.P) * g.rm;  // first staged row
+
+  // step table: LDS byte offset of each step's unit per lane group (units
+  // past the last tap read tap 0: the packed operand is zero there)
+  int* tab = reinterpret_cast<int*>(smem + g.tab_off);
+  for (int u = tid; u < 4 * g.steps; u += NT) {
+    if constexpr (MODE == SPLIT_IMAGE) {
+      const int Sp = (g.S + 1) / 2, r = u / Sp, sp = u - r * Sp;
+      tab[u] = r < g.R ? 16 * (r * g.in_wp + sp) : 0;
+    } else {
+      const int oct = u % g.co;
+      int tap = u / g.co;
+      if (MODE == SPLIT_POINT || tap >= g.R * g.S) tap = 0;
+      const int r = tap / g.S, s = tap - r * g.S;
+      const int a = r % g.sh, b = s % g.sw;
+      tab[u] = 16 * (oct * g.Epad + ((a * g.nb + b) * g.in_rows + r / g.sh) * g.in_wp + s / g.sw);
+    }
+  }
+
+  // Staging items of this thread: global byte offset (for IMAGE: of either
+  // pixel), LDS byte offset (24 bits) and octet.  Slots past the last item
+  // repeat the thread's previous one (the same bytes to the same place),
+  // which keeps the loop free of branches.
+  unsigned goff[NI], goff2[MODE == SPLIT_IMAGE ? NI : 1], loff[NI];
+  const int HW = g.H * g.W;
+  {
+    int it = tid < g.items ? tid : tid % g.items;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      if (i > 0 && it + NT < g.items) it += NT;
+      if constexpr (MODE == SPLIT_POINT) {
+        // consecutive lanes take the octets of one row: contiguous channels
+        const int e = fdiv(it, g.dv_nb), o = it - e * g.co;
+        loff[i] = 16u * (unsigned)(o * g.Epad + e) | ((unsigned)o << 24);
+        const int k = kt * BP + e;
+        goff[i] = k < g.K ? 4u * ((unsigned)k * (unsigned)g.C + 8u * (unsigned)o) : kOob;
+      } else {
+        const int o = fdiv(it, g.dv_E), e = it - o * g.E;
+        const int prow = fdiv(e, g.dv_wp), x = e - prow * g.in_wp;
+        const int f = fdiv(prow, g.dv_rows), row = prow - f * g.in_rows;
+        const int a = fdiv(f, g.dv_nb), b = f - a * g.nb;
+        const int nu = nu0 + row;
+        const int n = fdiv(nu, g.dv_Hi), yi = nu - n * g.Hi;
+        loff[i] = 16u * (unsigned)(o * g.Epad + e) | ((unsigned)o << 24);
+        if constexpr (MODE == SPLIT_IMAGE) {
+          const int y = yi - g.ph, xx = q0 * g.sw + 2 * x - g.pw;
+          const bool rok = n < g.N && (unsigned)y < (unsigned)g.H;
+          const unsigned base = (unsigned)(ISZ * ((n * g.C * g.H + y) * g.W + xx));
+          goff[i] = rok && (unsigned)xx < (unsigned)g.W ? base : kOob;
+          goff2[i] = rok && (unsigned)(xx + 1) < (unsigned)g.W ? base + ISZ : kOob;
+        } else {
+          const int y = yi * g.sh + a - g.ph, xx = (q0 + x) * g.sw + b - g.pw;
+          goff[i] = n < g.N && (unsigned)y < (unsigned)g.H && (unsigned)xx < (unsigned)g.W
+                        ? (unsigned)(ISZ * (((n * g.C + o * 8) * g.H + y) * g.W + xx))
+                        : kOob;
+        }
+      }
+    }
+  }
+  const auto irsrc = make_rsrc(MODE == SPLIT_POINT ? KerV : InV, g.st_bytes);
+  const auto prsrc = make_rsrc(Pk, g.pk_bytes);
+
+  unsigned stg[NI][8];
+  // Load e of item i of chunk ch (scalar offsets stay inside the tensor, so
+  // that the range check's difference is positive).
+  constexpr int LPI = MODE == SPLIT_POINT ? 2 : 8;  // loads per item
+  auto load_in = [&](int i, int e, int ch) {
+    if constexpr (MODE == SPLIT_POINT) {
+      const int c = ch * g.co * 8 + 4 * e;
+      const unsigned off = c + 8 * (int)(loff[i] >> 24) >= g.C ? kOob : goff[i];
+      const v4u v = __builtin_bit_cast(
+          v4u, __builtin_amdgcn_raw_buffer_load_b128(irsrc, off, min(c, g.C - 4) * 4, 0));
+#pragma unroll
+      for (int x = 0; x < 4; ++x) stg[i][4 * e + x] = v[x];
+    } else {
+      unsigned off;
+      int so;
+      if constexpr (MODE == SPLIT_IMAGE) {
+        off = (e & 3) >= g.C ? kOob : e < 4 ? goff[i] : goff2[i];
+        so = min(e & 3, g.C - 1) * HW * ISZ;
+      } else {
+        const int c = ch * g.co * 8 + e;
+        off = c + 8 * (int)(loff[i] >> 24) >= g.C ? kOob : goff[i];
+        so = min(c, g.C - 1) * HW * ISZ;
+      }
+      if constexpr (NPL == 3) stg[i][e] = __builtin_amdgcn_raw_buffer_load_b32(irsrc, off, so, 0);
+      else stg[i][e] = __builtin_amdgcn_raw_buffer_load_b16(irsrc, off, so, 0);
+    }
+  };
+  const int pl_bytes = g.co * g.Epad * 16;
+  // Conversion of an item in four pieces (pairs of values), then its LDS writes.
+  v4u cvt[NI][NPL];
+  auto convert_piece = [&](int i, int e, unsigned char* buf) {
+    if constexpr (NPL == 3) {
+      unsigned a, b, c;
+      split2(__builtin_bit_cast(float, stg[i][2 * e]), __builtin_bit_cast(float, stg[i][2 * e + 1]), a, b, c);
+      cvt[i][0][e] = a; cvt[i][1][e] = b; cvt[i][2][e] = c;
+    } else {
+      cvt[i][0][e] = (stg[i][2 * e] & 0xffffu) | (stg[i][2 * e + 1] << 16);
+    }
+    if (e == 3) {
+      unsigned char* d = buf + (loff[i] & 0xffffffu);
+#pragma unroll
+      for (int p = 0; p < NPL; ++p) *reinterpret_cast<v4u*>(d + p * pl_bytes) = cvt[i][p];
+    }
+  };
+
+  // LDS byte offset of this lane's staged row (output pixel) of each block
+  unsigned paddr[WP];
+#pragma unroll
+  for (int j = 0; j < WP; ++j) {
+    const int p = (wp * WP + j) * 16 + j16;
+    if constexpr (MODE == SPLIT_POINT) {
+      paddr[j] = 16u * (unsigned)p;
+    } else {
+      const int t = fdiv(p, g.dv_tw), col = p - t * g.tw;
+      const int rho = rho0 + t;
+      unsigned ad = 0;
+      if (t < g.tr && rho < rho_end) {
+        const int n = fdiv(rho, g.dv_P);
+        const int row = n * g.Hi + (rho - n * g.P) * g.rm - nu0;
+        ad = MODE == SPLIT_IMAGE ? 16u * (unsigned)(row * g.in_wp) + 8u * (unsigned)(col * g.cm)
+                                 : 16u * (unsigned)(row * g.in_wp + col);
+      }
+      paddr[j] = ad;
+    }
+  }
+
+  // packed operand: steps wc, wc + NWC, ... of each chunk
+  const int F = g.nchunks * g.steps;
+  const unsigned blk0 = (unsigned)((MODE == SPLIT_POINT ? rt : kt) * (BK / 16) + wk * WK);
+  auto load_a = [&](v4u (&a)[WK][NPL], int x, int ch, int m) {  // part x of step m of chunk ch
+    const unsigned f = (unsigned)min(ch * g.steps + m, F - 1);
+    a[x / NPL][x % NPL] = __builtin_bit_cast(
+        v4u, __builtin_amdgcn_raw_buffer_load_b128(prsrc, (unsigned)lane * 16u,
+                                                   (int)(((blk0 + x / NPL) * (unsigned)F + f) * NPL + x % NPL) * 1024, 0));
+  };
+
+  v4f acc[WK][WP], part[SEP ? WK : 1][SEP ? WP : 1];
+#pragma unroll
+  for (int i = 0; i < WK; ++i)
+#pragma unroll
+    for (int j = 0; j < WP; ++j) {
+      acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+      if constexpr (SEP) part[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+
+  constexpr int BD = OCC > 2 ? 2 : 3;
+  v4u bq[BD][NPL];  // LDS operands of this block and the BD - 1 next
+  auto load_b = [&](v4u (&b)[NPL], const unsigned char* buf, unsigned ad) {
+#pragma unroll
+    for (int p = 0; p < NPL; ++p) {
+      const unsigned char* s = buf + ad + p * pl_bytes;
+      if constexpr (MODE == SPLIT_IMAGE) {  // pixels are 8 bytes: an odd one is 8-byte aligned
+        const v2u lo = *reinterpret_cast<const v2u*>(s), hi = *reinterpret_cast<const v2u*>(s + 8);
+        b[p] = v4u{lo[0], lo[1], hi[0], hi[1]};
+      } else {
+        b[p] = *reinterpret_cast<const v4u*>(s);
+      }
+    }
+  };
+  auto mma1 = [&](const v4u& a, const v4u& b, v4f& c) {
+    const v8bf x = __builtin_bit_cast(v8bf, a), y = __builtin_bit_cast(v8bf, b);
+    c = MODE == SPLIT_POINT ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(y, x, c, 0, 0, 0)
+                            : __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, c, 0, 0, 0);
+  };
+  auto mma = [&](v4u (&a)[WK][NPL], v4u (&b)[NPL], int j) {
+    if constexpr (NPL == 3) {
+      // small products first
+      constexpr int PA[6] = {0, 2, 1, 0, 1, 0}, PB[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+      for (int i = 0; i < WK; ++i)
+#pragma unroll
+        for (int p = 0; p < 6; ++p) {
+          mma1(a[i][PA[p]], b[PB[p]], SEP && p < 5 ? part[i % (SEP ? WK : 1)][j % (SEP ? WP : 1)] : acc[i][j]);
+          __builtin_amdgcn_sched_barrier(0x7f6);  // MFMAs stay in this order
+        }
+    } else {
+#pragma unroll
+      for (int i = 0; i < WK; ++i) mma1(a[i][0], b[0], acc[i][j]);
+    }
+  };
+
+  // prologue: chunk 0 into buffer 0
+  v4u aq[AD + 1][WK][NPL];  // Ker operands of this step and the AD next
+#pragma unroll
+  for (int x = 0; x < WK * NPL; ++x) load_a(aq[0], x, 0, min(wc, g.steps - 1));
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int e = 0; e < LPI; ++e) load_in(i, e, 0);
+#pragma unroll
+  for (int d = 1; d < AD; ++d)
+#pragma unroll
+    for (int x = 0; x < WK * NPL; ++x) load_a(aq[d], x, d / NS, min((d % NS) * NWC + wc, g.steps - 1));
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) convert_piece(i, e, smem);
+  __syncthreads();
+
+  // Staging of the next chunk: an item's loads are issued LAG steps before
+  // its conversion.
+  static_assert(ONE || NS >= 2, "an item's loads and its conversion are in different steps");
+  constexpr int LAG = NS > 4 ? 3 : NS / 2;
+  constexpr int IPS = (NI + NS - LAG - 1) / (NS - LAG);  // items per step
+  for (int ch = 0; ch < (ONE ? 1 : g.nchunks); ++ch) {
+    const unsigned char* buf = smem + (ch & 1) * g.buf_bytes;
+    unsigned char* nbuf = smem + ((ch + 1) & 1) * g.buf_bytes;
+    int off = tab[4 * min(wc, g.steps - 1) + gq];
+    load_b(bq[0], buf, paddr[0] + off);
+    if constexpr (BD > 2) load_b(bq[1], buf, paddr[1 % WP] + off);
+    static_for<NS>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      constexpr int n1 = i + 1 < NS ? i + 1 : i;
+      const int offn = tab[4 * min(n1 * NWC + wc, g.steps - 1) + gq];
+      const bool run = NWC == 1 || i * NWC + wc < g.steps;
+      static_for<WP>([&](auto J) {
+        constexpr int j = decltype(J)::value;
+        constexpr int cur = (i * WP + j) % BD, ahead = j + BD - 1;
+        load_b(bq[(cur + BD - 1) % BD], buf, paddr[ahead % WP] + (ahead < WP ? off : offn));
+        // this region's share of the step's loads, spread out so that the four
+        // waves' loads don't queue up at the address unit: the Ker operands
+        // AD steps ahead (the next chunk's first steps at the end), then In items of the next chunk
+        constexpr int NV = WK * NPL + (ONE ? 0 : LPI * IPS);
+        static_for<NV>([&](auto Q) {
+          constexpr int q = decltype(Q)::value;
+          if constexpr (q * WP / NV == j && (!ONE || q < WK * NPL)) {
+            if constexpr (q < WK * NPL) {
+              load_a(aq[AD], q, ch + (i + AD) / NS, min(((i + AD) % NS) * NWC + wc, g.steps - 1));
+            } else {
+              constexpr int it = i * IPS + (q - WK * NPL) / LPI;
+              if constexpr (it < NI) load_in(it, (q - WK * NPL) % LPI, ch + 1);
+            }
+          }
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        if (run) mma(aq[0], bq[cur], j);
+        // this region's share of the step's conversions
+        constexpr int PC = 4 * IPS;
+        static_for<PC>([&](auto Q) {
+          constexpr int q = decltype(Q)::value;
+          if constexpr (!ONE && q * WP / PC == j && i >= LAG) {
+            constexpr int it = (i - LAG) * IPS + q / 4;
+            if constexpr (it < NI) convert_piece(it, q & 3, nbuf);
+          }
+        });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      off = offn;
+#pragma unroll
+      for (int d = 0; d < AD; ++d)
+#pragma unroll
+        for (int x = 0; x < WK; ++x)
+#pragma unroll
+          for (int p = 0; p < NPL; ++p) aq[d][x][p] = aq[d + 1][x][p];
+    });
+    if constexpr (!ONE || NWC > 1) __syncthreads();
+  }
+  if constexpr (SEP) {
+#pragma unroll
+    for (int i = 0; i < WK; ++i)
+#pragma unroll
+      for (int j = 0; j < WP; ++j) acc[i][j] += part[i][j];
+  }
+
+  // channel groups: sum in LDS, each group finishing its share of the blocks
+  if constexpr (NWC > 1) {
+    float* red = reinterpret_cast<float*>(smem);
+    constexpr int RT = WK * WP * 4;
+#pragma unroll
+    for (int i = 0; i < WK; ++i)
+#pragma unroll
+      for (int j = 0; j < WP; ++j)
+        *reinterpret_cast<v4f*>(red + ((wave * (RT / 4) + i * WP + j) * 64 + lane) * 4) = acc[i][j];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < WK; ++i)
+#pragma unroll
+      for (int j = 0; j < WP; ++j) {
+        if ((i * WP + j) % NWC != wc) continue;
+        v4f s = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < NWC; ++q)
+          s += *reinterpret_cast<const v4f*>(
+              red + (((q * NWK * NWP + wp * NWK + wk) * (RT / 4) + i * WP + j) * 64 + lane) * 4);
+        acc[i][j] = s;
+      }
+  }
+
+  // Block (i, j) holds output channels k0 + 0..3 and one pixel per lane.
+  const int PQ = g.P * g.Q;
+  auto locate = [&](int i, int j, int& n, int& h, int& q, int& k0) -> bool {
+    if constexpr (MODE == SPLIT_POINT) {
+      const int px = rt * BK + (wk * WK + i) * 16 + j16;
+      k0 = kt * BP + (wp * WP + j) * 16 + gq * 4;
+      n = fdiv(px, g.dv_PQ);
+      h = 0;
+      q = px - n * PQ;
+      return n < g.N;
+    } else {
+      const int p = (wp * WP + j) * 16 + j16;
+      const int t = fdiv(p, g.dv_tw), rho = rho0 + t;
+      k0 = kt * BK + (wk * WK + i) * 16 + gq * 4;
+      n = fdiv(rho, g.dv_P);
+      h = rho - n * g.P;
+      q = q0 + p - t * g.tw;
+      return t < g.tr && rho < rho_end && q < g.Q;
+    }
+  };
+  float z = 0.f;  // NaN once a stored output is not finite
+#pragma unroll
+  for (int j = 0; j < WP; ++j)
+#pragma unroll
+    for (int i = 0; i < WK; ++i) {
+      int n, h, q, k0;
+      const bool ok = locate(i, j, n, h, q, k0);
+      if (NWC > 1 && (i * WP + j) % NWC != wc) continue;
+      if (!ok) continue;
+      OT* o = Out + ((size_t)n * g.K + k0) * PQ + h * g.Q + q;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if (k0 + v >= g.K) continue;
+        const float x = acc[i][j][v];
+        z = __builtin_fmaf(x, 0.f, z);
+        o[(size_t)v * PQ] = (OT)(NPL == 3 ? x * kUnscale : x);
+      }
+    }
+  if (z != z) {
+#pragma clang loop unroll(disable)
+    for (int b = 0; b < WK * WP * 4; ++b) {
+      const int v = b & 3, i = (b >> 2) / WP, j = (b >> 2) - i * WP;
+      int n, h, q, k0;
+      const bool ok = locate(i, j, n, h, q, k0);
+      if (NWC > 1 && (b >> 2) % NWC != wc) continue;
+      const int k = k0 + v;
+      if (!ok || k >= g.K) continue;
+      OT* o = Out + ((size_t)n * g.K + k) * PQ + h * g.Q + q;
+      if (__builtin_fabsf((float)*o) < __builtin_inff()) continue;
+      if constexpr (MODE == SPLIT_POINT) {  // (q runs over the whole image)
+        h = q / g.Q;
+        q -= h * g.Q;
+      }
+      *o = (OT)repair<NPL>(InV, KerV, g, n, k, h, q);
+    }
+  }
+}
+
+typedef void (*SplitFnF)(const void*, const v4u*, const void*, float*, SplitGeom);
+typedef void (*SplitFnB)(const void*, const v4u*, const void*, __bf16*, SplitGeom);
+struct SplitInstance {
+  SplitConfig c;
+  SplitFnF f32;
+  SplitFnB bf16;  // bf16 Out (bf16 inputs only)
+};
+
+#define SPLIT_F32(ID, MODE, WK, WP, NWK, NWP, NWC, NI, NS, AD, ONE, OCC, SEP)                                  \
+  SplitInstance{SplitConfig{ID, MODE, WK, WP, NWK, NWP, NWC, 3, NI, NS, ONE, OCC},                         \
+                &split_conv_kernel<MODE, WK, WP, NWK, NWP, NWC, 3, NI, NS, AD, ONE, OCC, SEP, float>, nullptr}
+#define SPLIT_BF16(ID, MODE, WK, WP, NWK, NWP, NWC, NI, NS, AD, ONE, OCC, SEP)                                  \
+  SplitInstance{SplitConfig{ID, MODE, WK, WP, NWK, NWP, NWC, 1, NI, NS, ONE, OCC},                         \
+                &split_conv_kernel<MODE, WK, WP, NWK, NWP, NWC, 1, NI, NS, AD, ONE, OCC, SEP, float>,           \
+                &split_conv_kernel<MODE, WK, WP, NWK, NWP, NWC, 1, NI, NS, AD, ONE, OCC, SEP, __bf16>}
+
+const SplitInstance kSplit[] = {
+#include "split_instances.inc"
+};
+constexpr int kNumSplit = sizeof(kSplit) / sizeof(kSplit[0]);
+
+}  // namespace
+
+const SplitConfig* split_configs(int* count) {
+  static SplitConfig table[kNumSplit];
+  static const bool init = [] {
+    for (int i = 0; i < kNumSplit; ++i) table[i] = kSplit[i].c;
+    return true;
+  }();
+  (void)init;
+  *count = kNumSplit;
+  return table;
+}
+
+bool stream_capturing(void* stream) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(reinterpret_cast<hipStream_t>(stream), &cs) != hipSuccess) {
+    (void)hipGetLastError();  // (not this call's error to report)
+    return true;
+  }
+  return cs != hipStreamCaptureStatusNone;
+}
+
+int split_launch(const SplitPlan& p, bool out_bf16, const void* In, const void* Ker, void* Pk, void* Out,
+                 void* stream) {
+  const SplitInstance* inst = nullptr;
+  for (const SplitInstance& x : kSplit)
+    if (x.c.id == p.cfg->id) inst = &x;
+  if (!inst || (out_bf16 && !inst->bf16)) return CONV_EINVAL;
+  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  const SplitGeom& g = p.g;
+  const void* fn = out_bf16 ? reinterpret_cast<const void*>(inst->bf16) : reinterpret_cast<const void*>(inst->f32);
+  if (p.lds_bytes > 65536) {
+    // raise the kernel's dynamic LDS limit once
+    static std::mutex mu;
+    static bool done[2][kNumSplit] = {};
+    std::lock_guard<std::mutex> lk(mu);
+    bool& d = done[out_bf16][inst - kSplit];
+    if (!d) {
+      if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 163840) != hipSuccess) return CONV_EHIP;
+      d = true;
+    }
+  }
+  v4u* pk = static_cast<v4u*>(Pk);
+  if (p.cfg->mode == SPLIT_CONV) {
+    const int n = 8 * g.R * g.S, waves = g.blocks * g.nchunks * g.co;
+    const int lds = 4 * 16 * (n + 1) * (p.cfg->npl == 3 ? 4 : 2);
+    const FastDiv dv = make_fastdiv(n);
+    const bool f32 = p.cfg->npl == 3;
+    const auto pack = g.R * g.S == 9 ? (f32 ? &split_pack_taps_kernel<3, 9> : &split_pack_taps_kernel<1, 9>)
+                      : g.R * g.S == 1 ? (f32 ? &split_pack_taps_kernel<3, 1> : &split_pack_taps_kernel<1, 1>)
+                                       : (f32 ? &split_pack_taps_kernel<3, 0> : &split_pack_taps_kernel<1, 0>);
+    hipLaunchKernelGGL(pack, dim3((waves + 3) / 4), dim3(256), lds, st, Ker, pk, g, dv);
+  } else {
+    const dim3 grid((g.blocks * g.nchunks * g.steps + 3) / 4);
+    if (p.cfg->mode == SPLIT_POINT)
+      hipLaunchKernelGGL((split_pack_kernel<SPLIT_POINT, 3>), grid, dim3(256), 0, st, In, pk, g);
+    else if (p.cfg->npl == 3)
+      hipLaunchKernelGGL((split_pack_kernel<SPLIT_IMAGE, 3>), grid, dim3(256), 0, st, Ker, pk, g);
+    else
+      hipLaunchKernelGGL((split_pack_kernel<SPLIT_IMAGE, 1>), grid, dim3(256), 0, st, Ker, pk, g);
+  }
+  if (out_bf16)
+    hipLaunchKernelGGL(inst->bf16, dim3(g.num_tiles), dim3(p.cfg->threads()), p.lds_bytes, st, In, pk, Ker,
+                       static_cast<__bf16*>(Out), g);
+  else
+    hipLaunchKernelGGL(inst->f32, dim3(g.num_tiles), dim3(p.cfg->threads()), p.lds_bytes, st, In, pk, Ker,
+                       static_cast<float*>(Out), g);
+  return hipGetLastError() == hipSuccess ? CONV_OK : CONV_EHIP;
+}
+
+}  // namespace convfwd

@@ -1,0 +1,413 @@
+"""The split-operand kernels: layers that the compute calls run on them
+instead of on a tile plan (conv_fwd_split_plan).
+
+CPU: the kernels' index maps emulated from the exported launch fields (every
+staged slot an operand reads is written, every output stored once, the sum
+equal to the oracle), for every staging mode, strides, padding, tails of
+channels, rows and columns.  GPU: every compiled instance that the chooser
+selects over a range of layers against the oracle and against the tile plan
+(whose error in the 2-norm it must not exceed), bf16 Out, infinities and NaNs,
+extreme magnitudes, unaligned tensors, graph capture and tuning.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import conv as oconv
+from paper_2101_09808_amd import conv as B
+from paper_2101_09808_amd.workloads import ConvShape, make_inputs
+
+DEV = "cuda:0"
+CONV, IMAGE, POINT = 0, 1, 2
+
+
+def split_plan(s):
+    return B.conv_fwd_split_plan(*s.key(), s.stride, s.pad, B.CONV_DTYPE_BF16 if s.dtype == "bf16" else B.CONV_DTYPE_F32)
+
+
+def oracle(s, In, Ker):
+    return oconv.conv_fwd_ex(In.float().numpy(), Ker.float().numpy(), (s.stride,) * 2, (s.pad,) * 2)
+
+
+# ----------------------------------------------------------------- CPU
+
+def units(s, g, m):
+    """(octet of the chunk, tap) of the four lane groups of MFMA step m;
+    image mode: (kernel row, first of two columns)."""
+    for u in range(4 * m, 4 * m + 4):
+        if g["mode"] == IMAGE:
+            sp = (s.S + 1) // 2
+            yield u // sp, 2 * (u % sp)
+        else:
+            yield u % g["co"], u // g["co"]
+
+
+def emulate(s, g, In, Ker, wgs):
+    """Out and store counts of the given workgroups, in float64."""
+    N, C, K, H, W, R, S = s.key()
+    P, Q = s.P, s.Q
+    st, pd = s.stride, s.pad
+    out, written = np.zeros((N, K, P, Q)), np.zeros((N, K, P, Q), int)
+    point, image = g["mode"] == POINT, g["mode"] == IMAGE
+    BK, BP = 16 * g["wk"] * g["nwk"], 16 * g["wp"] * g["nwp"]
+    Cp = g["nchunks"] * g["co"] * 8
+    for b in wgs:
+        G8 = g["num_tiles"] & ~7
+        L = (b & 7) * (G8 >> 3) + (b >> 3) if b < G8 else b
+        if g["order"] == 0:
+            kt, rest = L % g["tiles_k"], L // g["tiles_k"]
+            ct, rt = rest % g["tiles_cols"], rest // g["tiles_cols"]
+        else:
+            ct, rest = L % g["tiles_cols"], L // g["tiles_cols"]
+            rt, kt = rest % g["tiles_rows"], rest // g["tiles_rows"]
+        rho0, rho_end = rt * g["tr"], min((rt + 1) * g["tr"], N * P)
+        q0 = ct * g["tw"]
+        n0 = rho0 // P
+        nu0 = n0 * g["Hi"] + (rho0 - n0 * P) * g["rm"]
+        # packed rows: Ker rows, or pixels of In
+        prow = np.arange(BK) + (rt if point else kt) * BK
+        acc = np.zeros((BK, BP))
+        for ch in range(g["nchunks"]):
+            lds = np.full((g["co"] * g["Epad"], 8), np.nan)
+            for it in range(g["items"]):
+                v = np.zeros(8)
+                if point:
+                    e, o = it // g["co"], it % g["co"]
+                    k = kt * BP + e
+                    c0 = (ch * g["co"] + o) * 8
+                    if k < K:
+                        n = max(0, min(8, C - c0))
+                        v[:n] = Ker[k, c0:c0 + n, 0, 0]
+                else:
+                    o, e = it // g["E"], it % g["E"]
+                    pr, x = e // g["in_wp"], e % g["in_wp"]
+                    f, row = pr // g["in_rows"], pr % g["in_rows"]
+                    a, bb = f // g["nb"], f % g["nb"]
+                    n, yi = divmod(nu0 + row, g["Hi"])
+                    if image:
+                        for p in range(2):
+                            y, xx = yi - pd, q0 * st + 2 * x + p - pd
+                            if n < N and 0 <= y < H and 0 <= xx < W:
+                                v[4 * p:4 * p + C] = In[n, :, y, xx]
+                    else:
+                        y, xx = yi * st + a - pd, (q0 + x) * st + bb - pd
+                        c0 = (ch * g["co"] + o) * 8
+                        if n < N and 0 <= y < H and 0 <= xx < W:
+                            m = max(0, min(8, C - c0))
+                            v[:m] = In[n, c0:c0 + m, y, xx]
+                lds[o * g["Epad"] + e] = v
+            assert g["items"] <= g["ni"] * 64 * g["nwk"] * g["nwp"] * g["nwc"]
+            flat = lds.reshape(-1)
+            for m in range(g["steps"]):
+                for uu in units(s, g, m):
+                    A = np.zeros((BK, 8))
+                    if image:
+                        r, s0 = uu
+                        off = 2 * 4 * (r * g["in_wp"] + s0 // 2) if r < R else 0
+                        for i, k in enumerate(prow):
+                            if k < K and r < R:
+                                for e in range(8):
+                                    if e % 4 < C and s0 + e // 4 < S:
+                                        A[i, e] = Ker[k, e % 4, r, s0 + e // 4]
+                    else:
+                        o, tap = uu
+                        real = o < g["co"] and tap < (1 if point else R * S)
+                        t = tap if real and not point else 0
+                        r, ss = t // S, t % S
+                        off = 8 * (o * g["Epad"] + ((r % st * g["nb"] + ss % st) * g["in_rows"] + r // st) * g["in_wp"]
+                                   + ss // st)
+                        c0 = (ch * g["co"] + o) * 8
+                        for i, k in enumerate(prow):
+                            n = max(0, min(8, C - c0))
+                            if not real:
+                                continue
+                            if point and k < N * P * Q:
+                                A[i, :n] = In[k // (P * Q), c0:c0 + n].reshape(n, -1)[:, k % (P * Q)]
+                            elif not point and k < K:
+                                A[i, :n] = Ker[k, c0:c0 + n, r, ss]
+                    for p in range(BP):
+                        if point:
+                            ad = 8 * p
+                        else:
+                            t, col = divmod(p, g["tw"])
+                            rho = rho0 + t
+                            if t >= g["tr"] or rho >= rho_end:
+                                continue
+                            n, h = divmod(rho, P)
+                            row = n * g["Hi"] + h * g["rm"] - nu0
+                            ad = 8 * row * g["in_wp"] + (4 * col * g["cm"] if image else 8 * col)
+                        vec = flat[ad + off:ad + off + 8]
+                        q = q0 + (p % g["tw"])
+                        if (p < BP and point) or q < Q:
+                            assert not np.isnan(vec).any(), "reads a slot that no item writes"
+                            acc[:, p] += A @ vec
+        for p in range(BP):
+            if point:
+                k = kt * BP + p
+                for i, px in enumerate(prow):
+                    if k < K and px < N * P * Q:
+                        n, x = divmod(px, P * Q)
+                        out[n, k, x // Q, x % Q] = acc[i, p]
+                        written[n, k, x // Q, x % Q] += 1
+                continue
+            t, col = divmod(p, g["tw"])
+            rho, q = rho0 + t, q0 + col
+            if t >= g["tr"] or rho >= rho_end or q >= Q:
+                continue
+            n, h = divmod(rho, P)
+            for i, k in enumerate(prow):
+                if k < K:
+                    out[n, k, h, q] = acc[i, p]
+                    written[n, k, h, q] += 1
+    return out, written
+
+
+# Layers on the route, for each staging mode: strides 1 and 2, padding, tails
+# of channels, output channels, rows and columns, tiles across images.
+EMULATED = [
+    ConvShape("sp_bf16_3x3_tails", 2, 20, 24, 9, 11, 3, 3, "bf16", 701, 1, 1),
+    ConvShape("sp_bf16_3x3_s2", 2, 12, 20, 13, 10, 3, 3, "bf16", 702, 2, 1),
+    ConvShape("sp_bf16_1x1", 2, 40, 24, 7, 9, 1, 1, "bf16", 703),
+    ConvShape("sp_bf16_1x1_s2", 3, 17, 20, 9, 9, 1, 1, "bf16", 704, 2, 0),
+    ConvShape("sp_bf16_3x3_c64", 1, 64, 40, 8, 10, 3, 3, "bf16", 705),
+]
+
+
+@pytest.mark.parametrize("s", EMULATED, ids=lambda s: s.name)
+def test_index_maps(s):
+    g = split_plan(s)
+    assert g and g["lds_bytes"] <= 160 * 1024
+    In, Ker = make_inputs(s)
+    out, written = emulate(s, g, In.double().numpy(), Ker.double().numpy(), range(g["num_tiles"]))
+    assert np.all(written == 1)
+    ref = oracle(s, In, Ker)
+    assert np.max(np.abs(out - ref)) <= 1e-9 * np.max(np.abs(ref))
+
+
+# larger layers, first, middle and last workgroups
+SAMPLED = [
+    ConvShape("sp_f32_3x3_c128", 32, 128, 128, 30, 30, 3, 3, "f32", 711),
+    ConvShape("sp_f32_3x3_c512", 32, 512, 512, 9, 9, 3, 3, "f32", 712),
+    ConvShape("sp_f32_3x3s2p1", 32, 64, 128, 56, 56, 3, 3, "f32", 713, 2, 1),
+    ConvShape("sp_f32_image_7x7s2", 32, 3, 64, 224, 224, 7, 7, "f32", 714, 2, 3),
+    ConvShape("sp_f32_image_3x3s2", 32, 3, 64, 224, 224, 3, 3, "f32", 715, 2, 1),
+    ConvShape("sp_f32_point", 1, 1024, 28269, 17, 17, 1, 1, "f32", 716),
+    ConvShape("sp_f32_1x1_c464", 2, 464, 176, 60, 60, 1, 1, "f32", 717),
+    ConvShape("sp_f32_3x3_odd", 23, 181, 92, 19, 19, 3, 3, "f32", 718),
+]
+
+
+@pytest.mark.parametrize("s", SAMPLED, ids=lambda s: s.name)
+def test_sampled_workgroups(s):
+    g = split_plan(s)
+    assert g
+    In, Ker = make_inputs(s)
+    T = g["num_tiles"]
+    few = dict(g, nchunks=1) if g["nchunks"] > 1 else g  # the first chunk of channels: the others only move the channel
+    nc = few["nchunks"] * g["co"] * 8 if g["mode"] != IMAGE else s.C
+    s1 = ConvShape(s.name, s.N, min(nc, s.C), s.K, s.H, s.W, s.R, s.S, s.dtype, s.seed, s.stride, s.pad)
+    In1, Ker1 = In[:, :nc].contiguous(), Ker[:, :nc].contiguous()
+    out, written = emulate(s1, few, In1.double().numpy(), Ker1.double().numpy(), sorted({0, T // 2, T - 1}))
+    hit = written == 1
+    assert written.max() == 1 and hit.any()
+    n = sorted(set(np.nonzero(hit)[0]))
+    sn = ConvShape(s.name, len(n), s1.C, s.K, s.H, s.W, s.R, s.S, s.dtype, s.seed, s.stride, s.pad)
+    ref = oracle(sn, In1[n].contiguous(), Ker1)
+    assert np.max(np.abs((out[n] - ref)[hit[n]])) <= 1e-9 * np.max(np.abs(ref))
+
+
+def test_route_needs_a_plan():
+    """A layer without a plan stays refused (7x7 taps, stride 1, three channels)."""
+    dims = (5, 3, 32, 220, 220, 7, 7)
+    with pytest.raises(B.ConvError) as e:
+        B.conv_fwd_ex_plan(*dims, 1, 3)
+    assert e.value.status == B.CONV_ENOPLAN
+    assert B.conv_fwd_split_plan(*dims, 1, 3) is None
+
+
+# ----------------------------------------------------------------- GPU
+
+def say(*a):
+    print(*a, flush=True)
+
+
+def run(s, In, Ker, out=None):
+    if s.stride != 1 or s.pad != 0:
+        return B.conv_fwd_ex(In, Ker, s.stride, s.pad, out=out)
+    return (B.conv_fwd_bf16 if s.dtype == "bf16" else B.conv_fwd)(In, Ker, out=out)
+
+
+def norm_err(out, ref):
+    return float(np.linalg.norm(out.double().cpu().numpy() - ref) / np.linalg.norm(ref))
+
+
+GPU_SHAPES = EMULATED + SAMPLED + [
+    ConvShape("sp_y18", 1, 512, 1024, 17, 17, 3, 3, "f32", 721, 1, 1),
+    ConvShape("sp_f32_c48_k570", 2, 48, 570, 31, 31, 3, 3, "f32", 722),
+    ConvShape("sp_f32_c144_93", 2, 144, 96, 93, 93, 3, 3, "f32", 723, 1, 1),
+    ConvShape("sp_f32_c181", 23, 181, 92, 19, 19, 3, 3, "f32", 724),
+    ConvShape("sp_f32_1x1_c165", 3, 165, 704, 60, 60, 1, 1, "f32", 725),
+    ConvShape("sp_f32_image_7x7", 5, 3, 64, 131, 131, 7, 7, "f32", 726, 2, 3),
+    ConvShape("sp_bf16_c288_1x1", 7, 288, 176, 79, 79, 1, 1, "bf16", 731),
+    ConvShape("sp_bf16_c128", 32, 128, 128, 28, 28, 3, 3, "bf16", 732, 1, 1),
+    ConvShape("sp_bf16_c144_k960", 3, 144, 960, 10, 10, 3, 3, "bf16", 733),
+    ConvShape("sp_bf16_c16_k792", 4, 16, 792, 89, 89, 3, 3, "bf16", 734),
+    ConvShape("sp_bf16_c832", 2, 832, 32, 58, 58, 3, 3, "bf16", 735, 1, 1),
+    ConvShape("sp_bf16_c32_136", 8, 32, 64, 136, 118, 3, 3, "bf16", 736),
+    ConvShape("sp_bf16_one_px", 2, 9, 20, 3, 3, 3, 3, "bf16", 737),
+    ConvShape("sp_bf16_5x5", 2, 24, 40, 14, 12, 5, 5, "bf16", 738),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("s", GPU_SHAPES, ids=lambda s: s.name)
+def test_parity(s):
+    """Every output against the oracle, poisoned Out with guards, two runs
+    equal; fp32: no further from the oracle than the tile plan."""
+    g = split_plan(s)
+    if g is None:
+        pytest.skip("on its tile plan")
+    In, Ker = make_inputs(s)
+    In_d, Ker_d = In.to(DEV), Ker.to(DEV)
+    n = s.N * s.K * s.P * s.Q
+    buf = torch.full((n + 128,), float("nan"), device=DEV)
+    buf[:64] = buf[-64:] = 7.0
+    out = buf[64:64 + n].view(s.N, s.K, s.P, s.Q)
+    say(f"[gpu] split {s.name} id={g['id']} tile={g['tr']}x{g['tw']} co={g['co']} wgs={g['num_tiles']}")
+    run(s, In_d, Ker_d, out)
+    first = out.clone()
+    run(s, In_d, Ker_d, out)
+    torch.cuda.synchronize()
+    assert torch.equal(first, out) and (buf[:64] == 7.0).all() and (buf[-64:] == 7.0).all()
+    ref = oracle(s, In, Ker)
+    got = out.cpu().numpy()
+    # fp32 sums: each product's and each sum's rounding is below 2^-22 of the largest partial sum
+    assert np.max(np.abs(got - ref)) <= 1e-5 * np.max(np.abs(ref))
+    if s.dtype == "f32" and s.stride == 1 and s.pad == 0:
+        plan = B.conv_fwd_with_plan(In_d, Ker_d, B.conv_fwd_plan(*s.key()))
+        torch.cuda.synchronize()
+        assert norm_err(out, ref) <= norm_err(plan, ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("s", [EMULATED[0], EMULATED[2], SAMPLED[0]], ids=lambda s: s.name)
+def test_integers_are_exact(s):
+    In, Ker = make_inputs(s, kind="int")
+    out = run(s, In.to(DEV), Ker.to(DEV))
+    torch.cuda.synchronize()
+    assert np.array_equal(out.double().cpu().numpy(), oracle(s, In, Ker))
+
+
+SPECIAL = [ConvShape("sp_nonfinite_f32", 8, 64, 64, 58, 58, 3, 3, "f32", 741),
+           ConvShape("sp_nonfinite_bf16", 2, 40, 24, 9, 11, 3, 3, "bf16", 742),
+           ConvShape("sp_nonfinite_image", 8, 3, 64, 224, 224, 7, 7, "f32", 743, 2, 3),
+           ConvShape("sp_nonfinite_point", 1, 512, 8192, 17, 17, 1, 1, "f32", 744)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("s", SPECIAL, ids=lambda s: s.name)
+def test_infinities_and_nans(s):
+    """Outputs that infinities, NaNs or overflowing sums touch are what IEEE
+    arithmetic gives; the others are unaffected."""
+    assert split_plan(s)
+    In, Ker = make_inputs(s)
+    In[0, 0, 2, 2], In[0, 1, 4, 5], In[0, 2, 6, 6] = float("inf"), float("-inf"), float("nan")
+    In[-1, 1, 3, 3] = 3e38
+    Ker[3, 0] = 1.0  # exact in bf16: its lower parts are zero
+    Ker[5, 1, 0, 0] = float("inf")
+    say(f"[gpu] non-finite {s.name}")
+    out = run(s, In.to(DEV), Ker.to(DEV))
+    torch.cuda.synchronize()
+    got = out.double().cpu()
+    ref = torch.nn.functional.conv2d(In.double(), Ker.double(), stride=s.stride, padding=s.pad)
+    assert torch.equal(torch.isnan(got), torch.isnan(ref))
+    big = ref.abs() > 3.3e38  # (an fp32 sum may overflow on the way there)
+    inf = torch.isinf(ref)
+    assert torch.equal(got[inf], ref[inf])
+    fin = torch.isfinite(ref) & ~big
+    assert torch.isfinite(got[fin]).all()
+    small = fin & (ref.abs() < 1e30)
+    assert (got[small] - ref[small]).abs().max() <= 1e-5 * ref[small].abs().max()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("scale_in,scale_ker", [(1e-30, 1e10), (1e-37, 1.0), (1e18, 1e18), (1e30, 1e-30), (2.0 ** -126, 2.0 ** 60)])
+def test_extreme_magnitudes(scale_in, scale_ker):
+    """The relative error does not depend on the operands' scale (the parts of
+    an operand stay in bf16's normal range), also where sums leave the scaled
+    range and are formed by plain fp32 arithmetic."""
+    s = SPECIAL[0]
+    In, Ker = make_inputs(s)
+    In, Ker = In * scale_in, Ker * scale_ker
+    out = run(s, In.to(DEV), Ker.to(DEV))
+    torch.cuda.synchronize()
+    ref = torch.nn.functional.conv2d(In.double(), Ker.double())
+    assert ((out.double().cpu() - ref).norm() / ref.norm()).item() <= 5e-7
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("s", [SAMPLED[0], EMULATED[0], SAMPLED[5]], ids=lambda s: s.name)
+def test_unaligned_tensors(s):
+    """In, Ker and Out one element past a 16-byte boundary."""
+    In, Ker = make_inputs(s)
+    ref = oracle(s, In, Ker)
+
+    def shifted(x):
+        b = torch.zeros(x.numel() + 8, dtype=x.dtype, device=DEV)
+        v = b[1:1 + x.numel()].view(x.shape)
+        v.copy_(x)
+        return v
+    out = shifted(torch.zeros(s.N, s.K, s.P, s.Q))
+    run(s, shifted(In), shifted(Ker), out)
+    torch.cuda.synchronize()
+    assert np.max(np.abs(out.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref))
+
+
+@pytest.mark.gpu
+def test_capture_and_side_streams():
+    """Under graph capture conv_fwd runs the tile plan (no workspace is taken
+    into the graph) and conv_fwd_ex_noalloc the split-operand kernels from its
+    static scratch; replays between eager calls give the eager results."""
+    s = SPECIAL[0]
+    In, Ker = make_inputs(s)
+    In_d, Ker_d = In.to(DEV), Ker.to(DEV)
+    ref = oracle(s, In, Ker)
+    a, b = (torch.zeros(s.N, s.K, s.P, s.Q, device=DEV) for _ in range(2))
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        B.conv_fwd(In_d, Ker_d, out=a)
+        B.conv_fwd_ex_noalloc(In_d, Ker_d, out=b)
+    st.synchronize()
+    eager = a.clone()
+    assert torch.equal(a, b)
+    say("[gpu] capture")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        B.conv_fwd(In_d, Ker_d, out=a)
+        B.conv_fwd_ex_noalloc(In_d, Ker_d, out=b)
+    for _ in range(3):
+        a.zero_()
+        b.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(b, eager)
+        assert np.max(np.abs(a.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref))
+        other = B.conv_fwd(In_d, Ker_d)
+        torch.cuda.synchronize()
+        assert torch.equal(other, eager)
+
+
+@pytest.mark.gpu
+def test_tuned_layer_keeps_the_faster_route():
+    s = ConvShape("sp_tuned", 4, 128, 128, 30, 30, 3, 3, "f32", 751)
+    In, Ker = make_inputs(s)
+    In_d, Ker_d = In.to(DEV), Ker.to(DEV)
+    ref = oracle(s, In, Ker)
+    out, plan, _ = B.conv_fwd_tune(In_d, Ker_d, top_n=3, reps=3)
+    torch.cuda.synchronize()
+    assert np.max(np.abs(out.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref))
+    planned = B.conv_fwd_with_plan(In_d, Ker_d, plan)
+    again = B.conv_fwd(In_d, Ker_d)
+    torch.cuda.synchronize()
+    assert np.max(np.abs(again.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref))
+    assert split_plan(s) is not None or torch.equal(again, planned)
