@@ -413,18 +413,18 @@ int conv_fwd_ex_plan(int N, int C, int K, int H, int W, int R, int S, int stride
  * fp32 arithmetic gives.
  * Writes min(cap, CONV_SPLIT_FIELDS) values: 1 if the split-operand kernels
  * run (else all zero), instance id, mode (0 In staged in LDS, 1 the same for
- * at most 4 channels, 2 Ker staged), 16-row blocks per wave of the packed and
+ * at most 4 channels, 2 Ker staged), pixels per staging load, 16-row blocks per wave of the packed and
  * the staged operand, waves along each, channel groups, parts per operand (3
  * or 1), staging items per thread, steps per chunk and group, 1 if one chunk;
  * tile rows and columns, row, column and k tiles, tile order, workgroups,
  * phases along rows and columns, staged rows per image, staged rows and
  * columns per output row and column, staged rows and items per row of a
  * tile, items and LDS slots per channel octet, octets per chunk, chunks,
- * steps per chunk, packed blocks, items per chunk, LDS bytes of a staging
+ * steps per chunk, packed blocks, items per chunk, pixel groups per staged row, LDS bytes of a staging
  * buffer, LDS offset of the step table, LDS bytes, packed bytes, estimated
  * time in us.  Returns CONV_SPLIT_FIELDS or a negative conv_status_t.
  */
-#define CONV_SPLIT_FIELDS 38
+#define CONV_SPLIT_FIELDS 40
 int conv_fwd_split_plan(int N, int C, int K, int H, int W, int R, int S, int stride_h, int stride_w, int pad_h,
                         int pad_w, int dtype, int32_t* out, int cap);
 

@@ -399,9 +399,9 @@ def conv_fwd_ex_geometry(N, C, K, H, W, R, S, stride, pad, plan):
 
 
 SPLIT_FIELDS = (
-    "use", "id", "mode", "wk", "wp", "nwk", "nwp", "nwc", "npl", "ni", "ns", "one",
+    "use", "id", "mode", "vec", "wk", "wp", "nwk", "nwp", "nwc", "npl", "ni", "ns", "one",
     "tr", "tw", "tiles_rows", "tiles_cols", "tiles_k", "order", "num_tiles", "na", "nb", "Hi", "rm", "cm",
-    "in_rows", "in_wp", "E", "Epad", "co", "nchunks", "steps", "blocks", "items", "buf_bytes", "tab_off",
+    "in_rows", "in_wp", "E", "Epad", "co", "nchunks", "steps", "blocks", "items", "ng", "buf_bytes", "tab_off",
     "lds_bytes", "pk_bytes", "us",
 )
 

@@ -41,14 +41,17 @@ struct SplitGeom {
   int nchunks, steps;       // chunks of 8 co channels; MFMA steps per chunk
   int blocks;               // 16-row blocks of the packed operand
   int items;                // staging items per chunk
+  int ng, E4;               // vector staging: groups of pixels per staged row, per octet
   unsigned st_bytes, pk_bytes;  // staged tensor, packed operand
   int buf_bytes, tab_off;   // LDS: bytes of one staging buffer, offset of the step table
-  FastDiv dv_E, dv_wp, dv_rows, dv_Hi, dv_P, dv_tw, dv_tiles_k, dv_tiles_cols, dv_tiles_rows, dv_nb, dv_PQ;
+  FastDiv dv_E, dv_wp, dv_rows, dv_Hi, dv_P, dv_tw, dv_tiles_k, dv_tiles_cols, dv_tiles_rows, dv_nb, dv_PQ, dv_Ez, dv_wpz;
 };
 
 // One compiled instance of the split kernel.
 struct SplitConfig {
-  int id, mode, wk, wp, nwk, nwp, nwc, npl;
+  int id, mode;
+  int vec;      // pixels per staging load (CONV: 1 or 4)
+  int wk, wp, nwk, nwp, nwc, npl;
   int ni;       // staging items per thread, at most
   int ns;       // MFMA steps per chunk and wave group
   int one;      // one chunk only

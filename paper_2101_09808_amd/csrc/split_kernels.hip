@@ -259,7 +259,7 @@ __device__ __forceinline__ float repair(const void* InV, const void* KerV, const
 // instructions of a step are spread over its blocks by hand (scheduling
 // barriers): left to itself the compiler waits for every LDS read right before its use
 // (68 us).
-template <int MODE, int WK, int WP, int NWK, int NWP, int NWC, int NPL, int NI, int NS, int AD, bool ONE, int OCC,
+template <int MODE, int VEC, int WK, int WP, int NWK, int NWP, int NWC, int NPL, int NI, int NS, int AD, bool ONE, int OCC,
           bool SEP, typename OT>
 __global__ void __launch_bounds__(NWK * NWP * NWC * 64, OCC)
 split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, const void* __restrict__ KerV,
@@ -315,8 +315,54 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
   // repeat the thread's previous one (the same bytes to the same place),
   // which keeps the loop free of branches.
   unsigned goff[NI], goff2[MODE == SPLIT_IMAGE ? NI : 1], loff[NI];
+  unsigned poff[VEC > 1 ? NI : 1][VEC];  // VEC: LDS byte offset of each pixel
   const int HW = g.H * g.W;
-  {
+  if constexpr (VEC > 1) {
+    // bf16 layers of one chunk, where single-pixel loads (128 bytes a wave)
+    // took most of the time: 32-channel layers with K = 32, 165x136 at batch 9
+    // 28.1 -> 18.8 us, 176x210 at batch 4 22.7 -> 16.1 us.  (fp32 layers did
+    // not gain: 3x3 C128 46.3 -> 49.8 us, C512 60.4 -> 60.6 us.)
+    // Four neighbouring input pixels per item, inside the image row: the last
+    // group of a row starts early enough to end in it (pixels staged twice
+    // get the same bytes).  Columns in the padding are zeroed here, in both
+    // buffers; no item writes them.
+    const int x0 = q0 * g.sw - g.pw;  // input column of the tile's first staged one
+    const int xa = max(x0, 0) & (NPL == 3 ? ~0 : ~1);  // bf16: dword-aligned groups
+    if (g.pw > 0) {
+      for (int u = tid; u < g.co * g.E; u += NT) {
+        const int o = fdiv(u, g.dv_Ez), e = u - o * g.E;
+        const int prow = fdiv(e, g.dv_wpz), x = e - prow * g.in_wp;
+        const int f = fdiv(prow, g.dv_rows);
+        const int xx = x0 + x * g.sw + f - fdiv(f, g.dv_nb) * g.nb;
+        if ((unsigned)xx < (unsigned)g.W) continue;
+        for (int p = 0; p < NPL; ++p)
+          for (int bf = 0; bf < (ONE ? 1 : 2); ++bf)
+            *reinterpret_cast<v4u*>(smem + bf * g.buf_bytes + (p * g.co + o) * g.Epad * 16 + e * 16) = v4u{0, 0, 0, 0};
+      }
+    }
+    int it = tid < g.items ? tid : tid % g.items;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      if (i > 0 && it + NT < g.items) it += NT;
+      const int o = fdiv(it, g.dv_E), e = it - o * g.E4;
+      const int prow = fdiv(e, g.dv_wp), gi = e - prow * g.ng;
+      const int a = fdiv(prow, g.dv_rows), row = prow - a * g.in_rows;
+      const int nu = nu0 + row;
+      const int n = fdiv(nu, g.dv_Hi), yi = nu - n * g.Hi;
+      const int y = yi * g.sh + a - g.ph, base = min(xa + 4 * gi, g.W - 4);
+      goff[i] = n < g.N && (unsigned)y < (unsigned)g.H
+                    ? (unsigned)(ISZ * (((n * g.C + o * 8) * g.H + y) * g.W + base))
+                    : kOob;
+      loff[i] = (unsigned)o;
+#pragma unroll
+      for (int p = 0; p < VEC; ++p) {
+        const int v = base + p - x0;  // staged column of the tile, all phases
+        const int ix = g.nb == 1 ? v : v >> 1, b = g.nb == 1 ? 0 : v & 1;
+        const bool in = v >= 0 && ix < g.in_wp;
+        poff[i][p] = 16u * (unsigned)(o * g.Epad + (in ? ((a * g.nb + b) * g.in_rows + row) * g.in_wp + ix : g.E));
+      }
+    }
+  } else {
     int it = tid < g.items ? tid : tid % g.items;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -353,7 +399,9 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
   const auto irsrc = make_rsrc(MODE == SPLIT_POINT ? KerV : InV, g.st_bytes);
   const auto prsrc = make_rsrc(Pk, g.pk_bytes);
 
-  unsigned stg[NI][8];
+  typedef unsigned stg_t __attribute__((ext_vector_type(VEC == 1 ? 2 : NPL == 3 ? 4 : 2)));
+  unsigned stg[VEC > 1 ? 1 : NI][8];
+  stg_t stv[VEC > 1 ? NI : 1][8];
   // Load e of item i of chunk ch (scalar offsets stay inside the tensor, so
   // that the range check's difference is positive).
   constexpr int LPI = MODE == SPLIT_POINT ? 2 : 8;  // loads per item
@@ -365,6 +413,14 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
           v4u, __builtin_amdgcn_raw_buffer_load_b128(irsrc, off, min(c, g.C - 4) * 4, 0));
 #pragma unroll
       for (int x = 0; x < 4; ++x) stg[i][4 * e + x] = v[x];
+    } else if constexpr (VEC > 1) {
+      const int c = ch * g.co * 8 + e;
+      const unsigned off = c + 8 * (int)loff[i] >= g.C ? kOob : goff[i];
+      const int so = min(c, g.C - 1) * HW * ISZ;
+      if constexpr (NPL == 3)
+        stv[i][e] = __builtin_bit_cast(stg_t, __builtin_amdgcn_raw_buffer_load_b128(irsrc, off, so, 0));
+      else
+        stv[i][e] = __builtin_bit_cast(stg_t, __builtin_amdgcn_raw_buffer_load_b64(irsrc, off, so, 0));
     } else {
       unsigned off;
       int so;
@@ -381,20 +437,28 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
     }
   };
   const int pl_bytes = g.co * g.Epad * 16;
-  // Conversion of an item in four pieces (pairs of values), then its LDS writes.
-  v4u cvt[NI][NPL];
-  auto convert_piece = [&](int i, int e, unsigned char* buf) {
+  // Conversion of an item in pieces (pairs of values; four per pixel), each
+  // pixel's LDS writes after its last.
+  constexpr int PPI = 4 * VEC;  // pieces per item
+  v4u cvt[VEC > 1 ? 1 : NI][NPL];
+  auto convert_piece = [&](int i, int q, unsigned char* buf) {
+    const int e = q & 3, px = q >> 2, ci = VEC > 1 ? 0 : i;
     if constexpr (NPL == 3) {
-      unsigned a, b, c;
-      split2(__builtin_bit_cast(float, stg[i][2 * e]), __builtin_bit_cast(float, stg[i][2 * e + 1]), a, b, c);
-      cvt[i][0][e] = a; cvt[i][1][e] = b; cvt[i][2][e] = c;
+      unsigned lo, hi, a, b, c;
+      if constexpr (VEC > 1) lo = stv[i][2 * e][px], hi = stv[i][2 * e + 1][px];
+      else lo = stg[i][2 * e], hi = stg[i][2 * e + 1];
+      split2(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi), a, b, c);
+      cvt[ci][0][e] = a; cvt[ci][1][e] = b; cvt[ci][2][e] = c;
+    } else if constexpr (VEC > 1) {
+      const unsigned lo = stv[i][2 * e][px >> 1], hi = stv[i][2 * e + 1][px >> 1];
+      cvt[ci][0][e] = px & 1 ? (lo >> 16) | (hi & 0xffff0000u) : (lo & 0xffffu) | (hi << 16);
     } else {
-      cvt[i][0][e] = (stg[i][2 * e] & 0xffffu) | (stg[i][2 * e + 1] << 16);
+      cvt[ci][0][e] = (stg[i][2 * e] & 0xffffu) | (stg[i][2 * e + 1] << 16);
     }
     if (e == 3) {
-      unsigned char* d = buf + (loff[i] & 0xffffffu);
+      unsigned char* d = buf + (VEC > 1 ? poff[VEC > 1 ? i : 0][px] : loff[i] & 0xffffffu);
 #pragma unroll
-      for (int p = 0; p < NPL; ++p) *reinterpret_cast<v4u*>(d + p * pl_bytes) = cvt[i][p];
+      for (int p = 0; p < NPL; ++p) *reinterpret_cast<v4u*>(d + p * pl_bytes) = cvt[ci][p];
     }
   };
 
@@ -489,14 +553,14 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
 #pragma unroll
   for (int i = 0; i < NI; ++i)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) convert_piece(i, e, smem);
+    for (int e = 0; e < PPI; ++e) convert_piece(i, e, smem);
   __syncthreads();
 
   // Staging of the next chunk: an item's loads are issued LAG steps before
   // its conversion.
   static_assert(ONE || NS >= 2, "an item's loads and its conversion are in different steps");
   constexpr int LAG = NS > 4 ? 3 : NS / 2;
-  constexpr int IPS = (NI + NS - LAG - 1) / (NS - LAG);  // items per step
+  constexpr int NR = (NS - LAG) * WP;  // regions (step, block) that convert, from LAG WP on
   for (int ch = 0; ch < (ONE ? 1 : g.nchunks); ++ch) {
     const unsigned char* buf = smem + (ch & 1) * g.buf_bytes;
     unsigned char* nbuf = smem + ((ch + 1) & 1) * g.buf_bytes;
@@ -512,31 +576,25 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
         constexpr int j = decltype(J)::value;
         constexpr int cur = (i * WP + j) % BD, ahead = j + BD - 1;
         load_b(bq[(cur + BD - 1) % BD], buf, paddr[ahead % WP] + (ahead < WP ? off : offn));
-        // this region's share of the step's loads, spread out so that the four
-        // waves' loads don't queue up at the address unit: the Ker operands
-        // AD steps ahead (the next chunk's first steps at the end), then In items of the next chunk
-        constexpr int NV = WK * NPL + (ONE ? 0 : LPI * IPS);
-        static_for<NV>([&](auto Q) {
+        // This region's share of the loads, spread out so that the waves'
+        // loads don't queue up at the address unit: the packed operands AD
+        // steps ahead (the next chunk's first steps at the end), and items of
+        // the next chunk, each item's within the LAG - 1 steps before the one
+        // that precedes its conversion.
+        static_for<WK * NPL>([&](auto Q) {
           constexpr int q = decltype(Q)::value;
-          if constexpr (q * WP / NV == j && (!ONE || q < WK * NPL)) {
-            if constexpr (q < WK * NPL) {
-              load_a(aq[AD], q, ch + (i + AD) / NS, min(((i + AD) % NS) * NWC + wc, g.steps - 1));
-            } else {
-              constexpr int it = i * IPS + (q - WK * NPL) / LPI;
-              if constexpr (it < NI) load_in(it, (q - WK * NPL) % LPI, ch + 1);
-            }
-          }
+          if constexpr (q * WP / (WK * NPL) == j)
+            load_a(aq[AD], q, ch + (i + AD) / NS, min(((i + AD) % NS) * NWC + wc, g.steps - 1));
+        });
+        if constexpr (!ONE) static_for<NI * LPI>([&](auto Q) {
+          constexpr int it = decltype(Q)::value / LPI, l = decltype(Q)::value % LPI;
+          if constexpr (it * NR / NI + l * (LAG - 1) * WP / LPI == i * WP + j) load_in(it, l, ch + 1);
         });
         __builtin_amdgcn_sched_barrier(0);
         if (run) mma(aq[0], bq[cur], j);
-        // this region's share of the step's conversions
-        constexpr int PC = 4 * IPS;
-        static_for<PC>([&](auto Q) {
+        if constexpr (!ONE) static_for<NI * PPI>([&](auto Q) {
           constexpr int q = decltype(Q)::value;
-          if constexpr (!ONE && q * WP / PC == j && i >= LAG) {
-            constexpr int it = (i - LAG) * IPS + q / 4;
-            if constexpr (it < NI) convert_piece(it, q & 3, nbuf);
-          }
+          if constexpr (LAG * WP + q * NR / (NI * PPI) == i * WP + j) convert_piece(q / PPI, q % PPI, nbuf);
         });
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -647,13 +705,13 @@ struct SplitInstance {
   SplitFnB bf16;  // bf16 Out (bf16 inputs only)
 };
 
-#define SPLIT_F32(ID, MODE, WK, WP, NWK, NWP, NWC, NI, NS, AD, ONE, OCC, SEP)                                  \
-  SplitInstance{SplitConfig{ID, MODE, WK, WP, NWK, NWP, NWC, 3, NI, NS, ONE, OCC},                         \
-                &split_conv_kernel<MODE, WK, WP, NWK, NWP, NWC, 3, NI, NS, AD, ONE, OCC, SEP, float>, nullptr}
-#define SPLIT_BF16(ID, MODE, WK, WP, NWK, NWP, NWC, NI, NS, AD, ONE, OCC, SEP)                                  \
-  SplitInstance{SplitConfig{ID, MODE, WK, WP, NWK, NWP, NWC, 1, NI, NS, ONE, OCC},                         \
-                &split_conv_kernel<MODE, WK, WP, NWK, NWP, NWC, 1, NI, NS, AD, ONE, OCC, SEP, float>,           \
-                &split_conv_kernel<MODE, WK, WP, NWK, NWP, NWC, 1, NI, NS, AD, ONE, OCC, SEP, __bf16>}
+#define SPLIT_F32(ID, MODE, VEC, WK, WP, NWK, NWP, NWC, NI, NS, AD, ONE, OCC, SEP)                                  \
+  SplitInstance{SplitConfig{ID, MODE, VEC, WK, WP, NWK, NWP, NWC, 3, NI, NS, ONE, OCC},                         \
+                &split_conv_kernel<MODE, VEC, WK, WP, NWK, NWP, NWC, 3, NI, NS, AD, ONE, OCC, SEP, float>, nullptr}
+#define SPLIT_BF16(ID, MODE, VEC, WK, WP, NWK, NWP, NWC, NI, NS, AD, ONE, OCC)                                  \
+  SplitInstance{SplitConfig{ID, MODE, VEC, WK, WP, NWK, NWP, NWC, 1, NI, NS, ONE, OCC},                         \
+                &split_conv_kernel<MODE, VEC, WK, WP, NWK, NWP, NWC, 1, NI, NS, AD, ONE, OCC, false, float>,           \
+                &split_conv_kernel<MODE, VEC, WK, WP, NWK, NWP, NWC, 1, NI, NS, AD, ONE, OCC, false, __bf16>}
 
 const SplitInstance kSplit[] = {
 #include "split_instances.inc"

@@ -80,12 +80,19 @@ bool split_geometry(const SplitShape& s, const SplitConfig& c, int tr, int tw, i
     const int64_t E = (int64_t)g.na * g.nb * in_rows * xcols;
     if (E > 16384) return false;
     g.E = (int)E;
-    g.Epad = (int)cdiv(E, 16) * 16;
+    g.Epad = (int)cdiv(E + (c.vec > 1 ? 1 : 0), 16) * 16;  // (vector staging: a slot for pixels outside the tile)
+    if (c.vec > 1) {
+      // groups of four pixels inside the image row; both column phases of a
+      // stride of 2; bf16 groups are dword-aligned
+      if (s.W < 4 || s.sw > 2 || g.nb != s.sw || (bf16 && s.W % 2)) return false;
+      g.ng = (int)cdiv(std::min<int64_t>(s.W, (int64_t)(tw - 1) * s.sw + s.S + (bf16 ? 1 : 0)), 4);
+      g.E4 = g.na * in_rows * g.ng;
+    }
     blocks = kt * (BK / 16);
     g.st_bytes = (unsigned)in_b;
   }
   if (chunks > 1 && c.one) return false;
-  g.items = co * g.E;
+  g.items = co * (c.vec > 1 ? g.E4 : g.E);
   if (g.items > c.ni * NT) return false;
   if (rows * cols * kt >= (int64_t(1) << 24)) return false;
   g.tiles_rows = (int)rows; g.tiles_cols = (int)cols; g.tiles_k = (int)kt;
@@ -102,8 +109,10 @@ bool split_geometry(const SplitShape& s, const SplitConfig& c, int tr, int tw, i
   const int lds = g.tab_off + 16 * g.steps;
   if (lds > kLds) return false;
   if (c.mode == SPLIT_CONV && 4 * 16 * (8 * s.R * s.S + 1) * e > 65536) return false;  // packing kernel's LDS
-  g.dv_E = make_fastdiv(g.E);
-  g.dv_wp = make_fastdiv(g.in_wp);
+  g.dv_E = make_fastdiv(c.vec > 1 ? g.E4 : g.E);
+  g.dv_wp = make_fastdiv(c.vec > 1 ? g.ng : g.in_wp);
+  g.dv_Ez = make_fastdiv(g.E);
+  g.dv_wpz = make_fastdiv(g.in_wp);
   g.dv_rows = make_fastdiv(g.in_rows);
   g.dv_Hi = make_fastdiv(g.Hi);
   g.dv_P = make_fastdiv(g.P);
@@ -136,7 +145,12 @@ double split_estimate(const SplitShape& s, const SplitPlan& p) {
   const double vmem = waves * (c.ni * (c.mode == SPLIT_POINT ? 2.0 : 8.0) + c.ns * c.wk * c.npl) * 17.0;
   const int res = std::max(1, std::min(c.occ * 4 / waves, kLds / p.lds_bytes));  // workgroups per CU
   const double per_cu = std::ceil((double)g.num_tiles / kCus);
-  const double out_us = (double)s.N * s.K * s.P * s.Q * 4.0 / 4.5e6;
+  // a tile writes runs of tw outputs, and 128-byte lines cut between
+  // workgroups cost twice (bf16 226x226 layer: 28-column tiles 111 us,
+  // 112-column ones 62 us); whole rows follow each other
+  const double run = g.tw * 4.0;
+  const double out_us = (double)s.N * s.K * s.P * s.Q * 4.0 / 4.5e6 *
+                        (c.mode == SPLIT_POINT || g.tw == s.Q ? 1.0 : (run + 124.0) / run);
   double main;
   if (res > 1 && per_cu > 1) {
     // workgroups on a CU overlap each other's loads, MFMAs and stores
@@ -146,6 +160,8 @@ double split_estimate(const SplitShape& s, const SplitPlan& p) {
     const double loop = g.nchunks * (mfma + vmem) * 0.95 / 1900.0;
     main = per_cu * (loop + 3.5) + out_us;
   }
+  // the staged halos, from the L2
+  main += (double)g.num_tiles * g.nchunks * g.items * 8.0 * (c.vec > 1 ? c.vec : 1) * (c.npl == 3 ? 4.0 : 2.0) / 12e6;
   const double pack = 5.0 + (double)p.pk_bytes * (c.npl == 3 ? 5.0 / 3 : 2.0) / 5.0e6;
   return pack + 0.88 * main;
 }
