@@ -132,6 +132,20 @@ def _stream_ptr(stream):
     return ctypes.c_void_p(s.cuda_stream)
 
 
+# A call of the smallest layers takes the GPU 6-8 us, and the host about as
+# long: the compute calls read the current stream's handle without building a
+# torch.cuda.Stream (where torch offers that), and look up their entry point,
+# the tensors' shapes and strides once.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+def _call_stream(stream):
+    if stream is None and _raw_stream is not None and _current_device is not None:
+        return _raw_stream(_current_device())
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
+
+
 def _check_inputs(In, Ker, dtype):
     if not (isinstance(In, torch.Tensor) and isinstance(Ker, torch.Tensor)):
         raise TypeError("In and Ker must be torch tensors")
@@ -139,12 +153,13 @@ def _check_inputs(In, Ker, dtype):
         raise ValueError("In and Ker must be GPU tensors (the library has no CPU path)")
     if In.dtype != dtype or Ker.dtype != dtype:
         raise TypeError(f"expected {dtype} tensors, got {In.dtype} and {Ker.dtype}")
-    if In.dim() != 4 or Ker.dim() != 4:
+    ish, ksh = In.shape, Ker.shape
+    if len(ish) != 4 or len(ksh) != 4:
         raise ValueError("In must be [N,C,H,W] and Ker [K,C,R,S]")
     if not (In.is_contiguous() and Ker.is_contiguous()):
         raise ValueError("In and Ker must be contiguous (NCHW / KCRS)")
-    N, C, H, W = In.shape
-    K, C2, R, S = Ker.shape
+    N, C, H, W = ish
+    K, C2, R, S = ksh
     if C2 != C:
         raise ValueError(f"channel mismatch: In has {C}, Ker has {C2}")
     return N, C, K, H, W, R, S
@@ -164,7 +179,7 @@ def conv_fwd(In, Ker, out=None, stream=None):
     """Eq. (1) for fp32 In [N,C,H,W] and Ker [K,C,R,S]; returns fp32 Out [N,K,P,Q]."""
     shape = _check_inputs(In, Ker, torch.float32)
     out = _out_for(In, shape, out)
-    st = lib().conv_fwd(*shape, In.data_ptr(), Ker.data_ptr(), out.data_ptr(), _stream_ptr(stream))
+    st = (_lib or lib()).conv_fwd(*shape, In.data_ptr(), Ker.data_ptr(), out.data_ptr(), _call_stream(stream))
     if st != CONV_OK:
         raise ConvError(st, "conv_fwd")
     return out
@@ -181,7 +196,7 @@ def conv_fwd_bf16(In, Ker, out=None, stream=None):
     """Eq. (1) for bf16 In and Ker, fp32 accumulation and fp32 Out."""
     shape = _check_inputs(In, Ker, torch.bfloat16)
     out = _out_for(In, shape, out)
-    st = lib().conv_fwd_bf16(*shape, In.data_ptr(), Ker.data_ptr(), out.data_ptr(), _stream_ptr(stream))
+    st = (_lib or lib()).conv_fwd_bf16(*shape, In.data_ptr(), Ker.data_ptr(), out.data_ptr(), _call_stream(stream))
     if st != CONV_OK:
         raise ConvError(st, "conv_fwd_bf16")
     return out
@@ -197,7 +212,7 @@ def conv_fwd_bf16_out(In, Ker, out=None, stream=None):
         out = torch.empty(oshape, dtype=torch.bfloat16, device=In.device)
     elif out.shape != oshape or out.dtype != torch.bfloat16 or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous bfloat16 {oshape} tensor")
-    st = lib().conv_fwd_bf16_out(*shape, In.data_ptr(), Ker.data_ptr(), out.data_ptr(), _stream_ptr(stream))
+    st = (_lib or lib()).conv_fwd_bf16_out(*shape, In.data_ptr(), Ker.data_ptr(), out.data_ptr(), _call_stream(stream))
     if st != CONV_OK:
         raise ConvError(st, "conv_fwd_bf16_out")
     return out
@@ -239,14 +254,17 @@ def _conv_fwd_ex(fn, In, Ker, stride, pad, out, stream):
     ph, pw = _pair(pad)
     bf16 = In.dtype == torch.bfloat16
     N, C, K, H, W, R, S = _check_inputs(In, Ker, torch.bfloat16 if bf16 else torch.float32)
-    inner = conv_fwd_ex_inner_shape(N, C, K, H, W, R, S, (sh, sw), (ph, pw))
-    P, Q = inner[7], inner[8]
+    # the output's extents; arguments out of range are left to the library
+    P, Q = ((H + 2 * ph - R) // sh + 1, (W + 2 * pw - S) // sw + 1) if sh > 0 and sw > 0 else (0, 0)
+    if out is None or out.shape != (N, K, P, Q):
+        inner = conv_fwd_ex_inner_shape(N, C, K, H, W, R, S, (sh, sw), (ph, pw))
+        P, Q = inner[7], inner[8]
     if out is None:
         out = torch.empty((N, K, P, Q), dtype=torch.float32, device=In.device)
     elif out.shape != (N, K, P, Q) or out.dtype != torch.float32 or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous float32 {(N, K, P, Q)} tensor")
-    st = getattr(lib(), fn)(N, C, K, H, W, R, S, sh, sw, ph, pw, CONV_DTYPE_BF16 if bf16 else CONV_DTYPE_F32,
-                            In.data_ptr(), Ker.data_ptr(), out.data_ptr(), _stream_ptr(stream))
+    st = getattr(_lib or lib(), fn)(N, C, K, H, W, R, S, sh, sw, ph, pw, CONV_DTYPE_BF16 if bf16 else CONV_DTYPE_F32,
+                                    In.data_ptr(), Ker.data_ptr(), out.data_ptr(), _call_stream(stream))
     if st != CONV_OK:
         raise ConvError(st, fn)
     return out
