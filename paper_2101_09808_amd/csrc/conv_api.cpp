@@ -417,12 +417,102 @@ int run_split(const SplitEntry& e, bool out_bf16, const void* In, const void* Ke
   return st == CONV_OK ? freed : st;
 }
 
+// Workspaces that the planned route takes for a call: their bytes summed, each
+// rounded up to the 256-byte alignment of the arena's bump allocation, and
+// the bytes of each level's kept buffer (a level's second workspace in one
+// call is a fresh allocation).  Mirrors the dispatch of run_ex, run_planned,
+// run_bf16_widened, launch (split partial sums) and launch_bf16_out; any
+// workspace the library carves is 256-byte aligned, which is what the
+// alignment of the plans that run on workspaces is computed with.
+size_t up256(size_t b) { return (b + 255) / 256 * 256; }
+
+struct Need {
+  size_t total = 0;
+  size_t level[3] = {0, 0, 0};
+  void add(int l, size_t bytes) {
+    total += up256(bytes);
+    if (level[l] == 0) level[l] = bytes;
+  }
+  void add_split(const Geom& g) {
+    if (g.split > 1) add(2, (size_t)g.split * g.N * g.K * g.P * g.Q * sizeof(float));
+  }
+};
+
+// run_bf16_widened: exact fp32 copies of In and Ker (and for bf16 Out the
+// fp32 one), then the fp32 plan
+int widened_need(const Shape& s, bool out_bf16, Need* need) {
+  const size_t n_in = (size_t)s.N * s.C * s.H * s.W, n_ker = (size_t)s.K * s.C * s.R * s.S;
+  const size_t n_out = out_bf16 ? (size_t)s.N * s.K * (s.H - s.R + 1) * (s.W - s.S + 1) : 0;
+  Entry e;
+  const int st = cached_entry(s, CONV_DTYPE_F32, ALIGN_ALL, &e);
+  if (st != CONV_OK) return st;
+  need->add(0, up256(n_in * 4) + up256(n_ker * 4) + n_out * 4);
+  need->add_split(e.g);
+  return CONV_OK;
+}
+
+int selected_need(const Shape& s, int dtype, int align, Need* need) {
+  Entry e;
+  const int st = cached_entry(s, dtype, align, &e);
+  if (st == CONV_ENOPLAN && dtype == CONV_DTYPE_BF16) return widened_need(s, false, need);
+  if (st == CONV_OK) need->add_split(e.g);
+  return st;
+}
+
+int bf16_out_need(const Shape& s, int align, bool pair_possible, Need* need) {
+  Entry e;
+  const int st = cached_entry_bf16_out(s, align, pair_possible, &e);
+  if (st == CONV_ENOPLAN) return widened_need(s, true, need);
+  if (st != CONV_OK) return st;
+  if (bf16_out_staged(*e.v)) {
+    need->add(1, (size_t)e.g.N * e.g.K * e.g.P * e.g.Q * sizeof(float));
+    need->add_split(e.g);
+  }
+  return CONV_OK;
+}
+
+int ex_need(const PhaseGeom& p, int dtype, const void* In, const void* Ker, Need* need) {
+  const Shape s{p.N, p.C, p.K, p.H, p.W, p.R, p.S};
+  if (p.sh == 1 && p.sw == 1 && p.ph == 0 && p.pw == 0) return selected_need(s, dtype, alignment_of(In, Ker), need);
+  const size_t e = dtype == CONV_DTYPE_BF16 ? 2 : 4;
+  const int Cp = p.C * p.na * p.nb;
+  const bool ker_moves = p.na * p.nb > 1;
+  const Shape inner{p.N, Cp, p.K, p.Hp, p.Wp, p.Rp, p.Sp};
+  // the plan runs on (aligned) phase images and the rearranged or the
+  // caller's Ker
+  const int ker_al = ker_moves ? ALIGN_KER : (alignment_of(In, Ker) & ALIGN_KER);
+  const int al_split = ALIGN_IN | ALIGN_IN4 | ker_al;
+  const size_t ker_ws = ker_moves ? (size_t)p.K * Cp * p.Rp * p.Sp * e : 0;
+  const size_t in_ws = up256((size_t)p.N * Cp * p.Hp * p.Wp * e);
+  if (dtype == CONV_DTYPE_F32) {
+    ExEntry x;
+    const int st = cached_ex_entry(p, (alignment_of(In, Ker) & (ALIGN_IN | ALIGN_IN4)) | ker_al, al_split, &x);
+    if (st != CONV_OK) return st;
+    need->add(0, (x.direct ? 0 : in_ws) + ker_ws);
+    need->add_split(x.e.g);
+    return CONV_OK;
+  }
+  need->add(0, in_ws + ker_ws);
+  return selected_need(inner, dtype, al_split, need);
+}
+
+// A call on the split-operand route keeps the buffers of its planned route
+// too: under graph capture the same call runs that, and a program that has
+// called the layer on this stream before captures no allocation.
+void reserve_planned(int st, const Need& need, void* stream) {
+  for (int l = 0; st == CONV_OK && l < 3; ++l)
+    if (need.level[l] > 0) st = workspace_reserve(l, need.level[l], stream);
+}
+
 int run_selected(const Shape& s, int dtype, const void* In, const void* Ker, float* Out, void* stream) {
   Entry e;
   const int st = routed_entry(s, dtype, alignment_of(In, Ker), &e);
-  if (takes_split(e, stream, false))
+  if (takes_split(e, stream, false)) {
+    Need need;
+    reserve_planned(selected_need(s, dtype, alignment_of(In, Ker), &need), need, stream);
     return run_split(split_entry(split_shape(s.N, s.C, s.K, s.H, s.W, s.R, s.S, 1, 1, 0, 0, dtype)), false, In, Ker, Out,
                      stream);
+  }
   if (st == CONV_ENOPLAN && dtype == CONV_DTYPE_BF16) return run_bf16_widened(s, In, Ker, Out, false, stream);
   if (st != CONV_OK) return st;
   return launch(*e.v, e.g, In, Ker, Out, stream);
@@ -478,10 +568,13 @@ int conv_fwd_bf16_out(int N, int C, int K, int H, int W, int R, int S, const uin
   Entry e;
   const Shape sh{N, C, K, H, W, R, S};
   routed_entry(sh, CONV_DTYPE_BF16, alignment_of(In, Ker), &e);
-  if (takes_split(e, stream, false))
+  const bool pair_possible = (W - S + 1) % 8 == 0 && (reinterpret_cast<uintptr_t>(Out) & 15) == 0;
+  if (takes_split(e, stream, false)) {
+    Need need;
+    reserve_planned(bf16_out_need(sh, alignment_of(In, Ker), pair_possible, &need), need, stream);
     return run_split(split_entry(split_shape(N, C, K, H, W, R, S, 1, 1, 0, 0, CONV_DTYPE_BF16)), true, In, Ker, Out,
                      stream);
-  const bool pair_possible = (W - S + 1) % 8 == 0 && (reinterpret_cast<uintptr_t>(Out) & 15) == 0;
+  }
   st = cached_entry_bf16_out(sh, alignment_of(In, Ker), pair_possible, &e);
   if (st == CONV_ENOPLAN) return run_bf16_widened(sh, In, Ker, Out, true, stream);
   if (st != CONV_OK) return st;
@@ -576,66 +669,6 @@ int run_ex(const PhaseGeom& p, int dtype, const void* In, const void* Ker, float
   return st == CONV_OK ? freed : st;
 }
 
-// Scratch bytes run_ex needs for these arguments, summed over the
-// workspaces it takes in order, each rounded up to the 256-byte alignment
-// of the arena's bump allocation.  Mirrors the dispatch of run_ex,
-// run_planned, run_bf16_widened and launch (split partial sums); any
-// workspace the library carves is 256-byte aligned, which is what the
-// alignment of the plans that run on workspaces is computed with.
-size_t up256(size_t b) { return (b + 255) / 256 * 256; }
-
-size_t split_need(const Geom& g) {
-  return g.split > 1 ? up256((size_t)g.split * g.N * g.K * g.P * g.Q * sizeof(float)) : 0;
-}
-
-int selected_need(const Shape& s, int dtype, int align, size_t* need) {
-  Entry e;
-  int st = cached_entry(s, dtype, align, &e);
-  if (st == CONV_ENOPLAN && dtype == CONV_DTYPE_BF16) {
-    // run_bf16_widened: exact fp32 copies of In and Ker, then the fp32 plan
-    const size_t n_in = (size_t)s.N * s.C * s.H * s.W, n_ker = (size_t)s.K * s.C * s.R * s.S;
-    const size_t wide = up256(up256(n_in * 4) + up256(n_ker * 4));
-    st = cached_entry(s, CONV_DTYPE_F32, ALIGN_ALL, &e);
-    if (st != CONV_OK) return st;
-    *need = wide + split_need(e.g);
-    return CONV_OK;
-  }
-  if (st != CONV_OK) return st;
-  *need = split_need(e.g);
-  return CONV_OK;
-}
-
-int ex_need(const PhaseGeom& p, int dtype, const void* In, const void* Ker, size_t* need) {
-  const Shape s{p.N, p.C, p.K, p.H, p.W, p.R, p.S};
-  if (p.sh == 1 && p.sw == 1 && p.ph == 0 && p.pw == 0) return selected_need(s, dtype, alignment_of(In, Ker), need);
-  const size_t e = dtype == CONV_DTYPE_BF16 ? 2 : 4;
-  const int Cp = p.C * p.na * p.nb;
-  const bool ker_moves = p.na * p.nb > 1;
-  const Shape inner{p.N, Cp, p.K, p.Hp, p.Wp, p.Rp, p.Sp};
-  if (dtype == CONV_DTYPE_F32) {
-    const int ker_al = ker_moves ? ALIGN_KER : (alignment_of(In, Ker) & ALIGN_KER);
-    const int al_direct = (alignment_of(In, Ker) & (ALIGN_IN | ALIGN_IN4)) | ker_al;
-    const int al_split = ALIGN_IN | ALIGN_IN4 | ker_al;
-    ExEntry x;
-    const int st = cached_ex_entry(p, al_direct, al_split, &x);
-    if (st != CONV_OK) return st;
-    const size_t in_ws = x.direct ? 0 : up256((size_t)p.N * Cp * p.Hp * p.Wp * e);
-    const size_t ker_ws = ker_moves ? (size_t)p.K * Cp * p.Rp * p.Sp * e : 0;
-    *need = (in_ws + ker_ws ? up256(in_ws + ker_ws) : 0) + split_need(x.e.g);
-    return CONV_OK;
-  }
-  const size_t in_bytes = up256((size_t)p.N * Cp * p.Hp * p.Wp * e);
-  const size_t ker_bytes = ker_moves ? (size_t)p.K * Cp * p.Rp * p.Sp * e : 0;
-  // the inner plan runs on the (aligned) phase images and the rearranged or
-  // the caller's Ker
-  const int align = ALIGN_IN | ALIGN_IN4 | (ker_moves ? ALIGN_KER : (alignment_of(In, Ker) & ALIGN_KER));
-  size_t inner_need = 0;
-  const int st = selected_need(inner, dtype, align, &inner_need);
-  if (st != CONV_OK) return st;
-  *need = up256(in_bytes + ker_bytes) + inner_need;
-  return CONV_OK;
-}
-
 // Installs an arena on the calling thread for the lifetime of the guard.
 struct ArenaGuard {
   explicit ArenaGuard(ScratchArena* a) { set_thread_arena(a); }
@@ -658,9 +691,12 @@ int conv_fwd_ex(int N, int C, int K, int H, int W, int R, int S, int stride_h, i
   ExEntry x;
   const int rt = ex_route(p, dtype, In, Ker, stream, false, &split, &x);
   if (rt != CONV_OK) return rt;
-  if (split)
+  if (split) {
+    Need need;
+    reserve_planned(ex_need(p, dtype, In, Ker, &need), need, stream);
     return run_split(split_entry(split_shape(N, C, K, H, W, R, S, stride_h, stride_w, pad_h, pad_w, dtype)), false, In,
                      Ker, Out, stream);
+  }
   return run_ex(p, dtype, In, Ker, Out, stream, x);
 }
 
@@ -671,9 +707,10 @@ int conv_fwd_ex_noalloc(int N, int C, int K, int H, int W, int R, int S, int str
   if (st != CONV_OK) return st;
   if (!In || !Ker || !Out) return CONV_ENULL;
   if (dtype != CONV_DTYPE_F32 && dtype != CONV_DTYPE_BF16) return CONV_EINVAL;
-  size_t need = 0;
-  st = ex_need(p, dtype, In, Ker, &need);
+  Need planned;
+  st = ex_need(p, dtype, In, Ker, &planned);
   if (st != CONV_OK) return st;
+  size_t need = planned.total;
   if (need > (size_t)CONV_NOALLOC_SCRATCH_BYTES) return CONV_ESCRATCH;
   bool split = false;
   ExEntry x;

@@ -106,6 +106,8 @@ bool resolve_geom(const Shape& s, const Variant& v, const conv_plan_t& plan, Geo
 
 // Launch the kernel of variant v (asynchronous).  Returns a conv_status_t.
 int launch(const Variant& v, const Geom& g, const void* In, const void* Ker, float* Out, void* stream);
+// Does launch_bf16_out stage this kernel's fp32 Out in a level 1 workspace?
+bool bf16_out_staged(const Variant& v);
 // Launch of a bf16-input plan writing bf16 Out (round to nearest even): the
 // transposing bf16 kernel writes it directly; other kernels write fp32 to a
 // stream-ordered workspace that a second kernel rounds into Out.
@@ -149,6 +151,9 @@ struct Workspace {
 };
 int workspace_acquire(int level, size_t bytes, void* stream, Workspace* w);
 int workspace_release(const Workspace& w, void* stream);
+// Grows the buffer kept for the stream and level to at least `bytes` unless
+// another host thread holds it.
+int workspace_reserve(int level, size_t bytes, void* stream);
 // Frees (stream-ordered) the buffers kept for `stream` on the current device.
 int workspace_release_stream(void* stream);
 // Allocation-free calls: while an arena is installed on the calling thread,

@@ -2272,6 +2272,25 @@ thread_local ScratchArena* t_arena = nullptr;
 
 void set_thread_arena(ScratchArena* a) { t_arena = a; }
 
+static int grow_kept(CachedWorkspace& c, size_t bytes, void* stream) {
+  if (c.size >= bytes) return CONV_OK;
+  if (c.ptr && stream_free(c.ptr, stream) != CONV_OK) return CONV_EHIP;
+  c.ptr = nullptr;
+  c.size = 0;
+  const size_t sz = (bytes + (size_t(1) << 20) - 1) >> 20 << 20;  // whole MiB
+  if (stream_alloc(sz, stream, &c.ptr) != CONV_OK) return CONV_EHIP;
+  c.size = sz;
+  return CONV_OK;
+}
+
+int workspace_reserve(int level, size_t bytes, void* stream) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return CONV_EHIP;
+  std::lock_guard<std::mutex> lk(g_ws_mu);
+  CachedWorkspace& c = g_ws[std::make_tuple(dev, stream, level)];
+  return c.busy ? CONV_OK : grow_kept(c, bytes, stream);
+}
+
 int workspace_acquire(int level, size_t bytes, void* stream, Workspace* w) {
   w->cached = false;
   w->arena = false;
@@ -2291,14 +2310,7 @@ int workspace_acquire(int level, size_t bytes, void* stream, Workspace* w) {
     std::lock_guard<std::mutex> lk(g_ws_mu);
     CachedWorkspace& c = g_ws[std::make_tuple(dev, stream, level)];
     if (!c.busy) {
-      if (c.size < bytes) {
-        if (c.ptr && stream_free(c.ptr, stream) != CONV_OK) return CONV_EHIP;
-        c.ptr = nullptr;
-        c.size = 0;
-        const size_t sz = (bytes + (size_t(1) << 20) - 1) >> 20 << 20;  // whole MiB
-        if (stream_alloc(sz, stream, &c.ptr) != CONV_OK) return CONV_EHIP;
-        c.size = sz;
-      }
+      if (grow_kept(c, bytes, stream) != CONV_OK) return CONV_EHIP;
       c.busy = true;
       w->ptr = c.ptr;
       w->cached = true;
@@ -2371,6 +2383,11 @@ int launch_round_bf16(const float* src, void* dst, int64_t n, void* stream) {
   hipLaunchKernelGGL(round_bf16_kernel, dim3(blocks), dim3(256), 0, reinterpret_cast<hipStream_t>(stream), src,
                      static_cast<unsigned short*>(dst), n);
   return hipGetLastError() == hipSuccess ? CONV_OK : CONV_EHIP;
+}
+
+bool bf16_out_staged(const Variant& v) {
+  const Instance* inst = find_instance(v.id);
+  return inst && !inst->bf16_outb;
 }
 
 int launch_bf16_out(const Variant& v, const Geom& g, const void* In, const void* Ker, void* Out, void* stream) {

@@ -439,6 +439,50 @@ def test_capture_and_side_streams():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("s,bf16_out", [
+    (ConvShape("sp_cap_bf16_s2", 8, 64, 128, 28, 28, 3, 3, "bf16", 761, 2, 1), False),
+    (ConvShape("sp_cap_f32_s2", 32, 64, 128, 56, 56, 3, 3, "f32", 762, 2, 1), False),
+    (ConvShape("sp_cap_bf16_5x5", 4, 64, 64, 24, 24, 5, 5, "bf16", 763), False),
+    (ConvShape("sp_cap_bf16_out", 4, 128, 128, 30, 30, 3, 3, "bf16", 764), True),
+], ids=lambda v: getattr(v, "name", None))
+def test_capture_of_a_layer_whose_plan_needs_workspaces(s, bf16_out):
+    """One eager call on a stream keeps the planned route's workspaces as well
+    as the packed operand's, so the capture on that stream allocates nothing,
+    and replays and eager calls in between agree."""
+    assert split_plan(s), "layer is not on the split-operand route"
+    In, Ker = make_inputs(s)
+    In_d, Ker_d = In.to(DEV), Ker.to(DEV)
+    ref = oracle(s, In, Ker)
+    tol = 2.0 ** -8 if bf16_out else 1e-5  # bf16 Out: half a unit of 8 bits
+
+    def call(out=None):
+        if bf16_out:
+            return B.conv_fwd_bf16_out(In_d, Ker_d, out=out)
+        return B.conv_fwd_ex(In_d, Ker_d, s.stride, s.pad, out=out)
+
+    def check(x):
+        torch.cuda.synchronize()
+        assert np.max(np.abs(x.float().cpu().numpy() - ref)) <= tol * np.max(np.abs(ref))
+
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        out = call()
+    check(out)
+    say(f"[gpu] capture {s.name}")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        call(out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        check(out)
+        with torch.cuda.stream(st):
+            other = call()
+        check(other)
+    B.release_workspaces(st)
+
+
+@pytest.mark.gpu
 def test_tuned_layer_keeps_the_faster_route():
     s = ConvShape("sp_tuned", 4, 128, 128, 30, 30, 3, 3, "f32", 751)
     In, Ker = make_inputs(s)
