@@ -379,12 +379,10 @@ def traffic_run(layers, launches=6):
         Ker = torch.empty(c.K, c.C, c.R, c.S, device=dev).uniform_(-1, 1).to(edt)
         outs = [torch.empty(c.N, c.K, c.P, c.Q, device=dev) for _ in range(nsets)]
         torch.cuda.synchronize()
-        sp = torch.cuda.current_stream().cuda_stream
+        # (conv_fwd would take the split-operand kernels where they are faster)
+        plan = B.conv_fwd_plan(*c.key(), dtype=B.CONV_DTYPE_BF16 if bf16 else B.CONV_DTYPE_F32)
         for i in range(launches):
-            st = B.conv_fwd_ptr(*c.key(), ins[i % nsets].data_ptr(), Ker.data_ptr(), outs[i % nsets].data_ptr(),
-                                sp, bf16)
-            if st != B.CONV_OK:
-                raise B.ConvError(st, "conv_fwd")
+            B.conv_fwd_with_plan(ins[i % nsets], Ker, plan, out=outs[i % nsets])
         torch.cuda.synchronize()
         del ins, outs, Ker
         print(f"traffic run: {launches} launches of {c.name}", flush=True)
@@ -1295,9 +1293,12 @@ def main():
             lk = lr["mean_kernel_ms"] * 1e-3
             lpeak = PEAK["bf16_mfma_tflops"] if lc.dtype == "bf16" else PEAK["fp32_mfma_tflops"]
             lplan = B.conv_fwd_plan(*lc.key(), dtype=B.CONV_DTYPE_BF16 if lc.dtype == "bf16" else B.CONV_DTYPE_F32)
+            lsplit = B.conv_fwd_split_plan(*lc.key(), dtype=B.CONV_DTYPE_BF16 if lc.dtype == "bf16" else B.CONV_DTYPE_F32)
             layers[lc.name] = {
                 "dtype": lc.dtype, "variant": lplan["variant"], "split_c": lplan["split_c"],
                 "num_wg": lplan["num_wg"],
+                # the split-operand instance that runs instead of the plan, if one does
+                "split_operand": lsplit["id"] if lsplit else None,
                 "kernel_us": lk * 1e6, "gflops": flops(lc) / lk / 1e9,
                 "pct_fp32_mfma_peak": 100 * flops(lc) / lk / 1e12 / PEAK["fp32_mfma_tflops"],
                 "pct_dtype_mfma_peak": 100 * flops(lc) / lk / 1e12 / lpeak,
@@ -1306,7 +1307,7 @@ def main():
                 "cold": lcold,
                 "cold_pct_fp32_mfma_peak_at_mean": 100 * flops(lc) / (lcold["mean_us"] * 1e-6) / 1e12
                 / PEAK["fp32_mfma_tflops"],
-                "traffic": counters.get((lc.name, plan_kernel_hash(lc, lplan))),
+                "traffic": None if lsplit else counters.get((lc.name, plan_kernel_hash(lc, lplan))),
             }
             if not args.no_cpu:
                 layers[lc.name]["cpu_oracle"] = cpu_baseline(lc, budget_s=3.0)
@@ -1333,7 +1334,9 @@ def main():
             del lrun
             inner = B.conv_fwd_ex_inner_shape(*lc.key(), lc.stride, lc.pad)
             lplan, ldirect = B.conv_fwd_ex_plan(*lc.key(), lc.stride, lc.pad)
+            lsplit = B.conv_fwd_split_plan(*lc.key(), lc.stride, lc.pad)
             layers[lc.name] = {
+                "split_operand": lsplit["id"] if lsplit else None,
                 "dtype": lc.dtype, "stride": lc.stride, "pad": lc.pad, "inner_shape": list(inner[:7]),
                 "variant": lplan["variant"], "split_c": lplan["split_c"], "direct": ldirect,
                 "kernel_us": lk * 1e6,
