@@ -373,8 +373,13 @@ SplitEntry split_entry(const SplitShape& s) {
   // Estimates of grids that fill half the chip are within a few percent of each
   // other's errors; for fewer tiles both are less reliable (a 672 x 814 1x1
   // layer on 6 tiles: estimate 30 against 32 us, measured 30.0 against 23.3).
+  // fp32 plans estimated below 26 us need 12%: over 260 random layers the 11
+  // routed ones between the two lines ran in 0.83 to 1.19 times their plan's
+  // speed (0.98 in the mean; 3x3 C48 K304 33x33 at batch 2 14.1 -> 16.9 us;
+  // the six between 26 and 36 us in 0.98 to 4.0 times).
   e.use = planned_time(s, &us) == CONV_OK && split_choose(s, &e.p) &&
-          e.p.pk_bytes <= (size_t)CONV_NOALLOC_SCRATCH_BYTES && e.p.us < (e.p.g.num_tiles >= 128 ? 0.97 : 0.9) * us;
+          e.p.pk_bytes <= (size_t)CONV_NOALLOC_SCRATCH_BYTES &&
+          e.p.us < (s.dtype == CONV_DTYPE_F32 && us < 26 ? 0.88 : e.p.g.num_tiles >= 128 ? 0.97 : 0.9) * us;
   std::lock_guard<std::mutex> lk(g_mu);
   g_split_cache[key] = e;
   return e;
