@@ -94,7 +94,8 @@ bool split_geometry(const SplitShape& s, const SplitConfig& c, int tr, int tw, i
   if (chunks > 1 && c.one) return false;
   g.items = co * (c.vec > 1 ? g.E4 : g.E);
   if (g.items > c.ni * NT) return false;
-  if (rows * cols * kt >= (int64_t(1) << 24)) return false;
+  // a grid dimension takes fewer than 2^32 threads
+  if (rows * cols * kt >= (int64_t(1) << 24) || rows * cols * kt * NT >= (int64_t(1) << 32)) return false;
   g.tiles_rows = (int)rows; g.tiles_cols = (int)cols; g.tiles_k = (int)kt;
   g.num_tiles = (int)(rows * cols * kt);
   g.nchunks = (int)chunks; g.steps = (int)steps;

@@ -266,6 +266,17 @@ def test_route_needs_a_plan():
     assert B.conv_fwd_split_plan(*dims, 1, 3) is None
 
 
+@pytest.mark.parametrize("dims", [(298261, 1, 2, 60, 60, 5, 5), (65535, 1, 2, 128, 128, 5, 5),
+                                  (1369568, 1, 2, 28, 28, 5, 5)], ids=str)
+def test_grid_fits_a_launch(dims):
+    """A grid dimension takes fewer than 2^32 threads: layers whose split grid
+    would be larger stay on the widened fp32 plan."""
+    g = B.conv_fwd_split_plan(*dims, dtype=B.CONV_DTYPE_BF16)
+    assert g is None or g["num_tiles"] * 64 * g["nwk"] * g["nwp"] * g["nwc"] < 2 ** 32
+    plan = B.conv_fwd_plan(*dims)  # of the widened inputs
+    assert plan["num_wg"] * B.conv_fwd_geometry(*dims, plan)["threads"] < 2 ** 32
+
+
 # ----------------------------------------------------------------- GPU
 
 def say(*a):
