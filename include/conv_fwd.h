@@ -408,9 +408,12 @@ int conv_fwd_ex_plan(int N, int C, int K, int H, int W, int R, int S, int stride
  * channels: In) into a per-stream workspace on every call, so under graph
  * capture conv_fwd, conv_fwd_bf16, conv_fwd_bf16_out and conv_fwd_ex run the
  * plan; conv_fwd_ex_noalloc packs into its static scratch and takes the same
- * route with and without capture.  Outputs that come out infinite or NaN are
- * formed again by plain fp32 sums, so infinities, NaNs and overflow give what
- * fp32 arithmetic gives.
+ * route with and without capture.  fp32 sums
+ * beyond 2^80, infinities and NaNs leave the split operands' range: a tile
+ * (workgroup) with an output that comes out infinite or NaN is computed again
+ * for these on the fp32 MFMAs, so they are what fp32 arithmetic gives; an fp32
+ * call whose every tile does so takes up to 3.5 times as long (bf16 calls: as
+ * long as ever).
  * Writes min(cap, CONV_SPLIT_FIELDS) values: 1 if the split-operand kernels
  * run (else all zero), instance id, mode (0 In staged in LDS, 1 the same for
  * at most 4 channels, 2 Ker staged), pixels per staging load, 16-row blocks per wave of the packed and

@@ -7,8 +7,8 @@
 // the other six, summed in fp32 by the MFMAs, give the product at fp32
 // precision for 6/16 of the fp32 MFMA's time.  Operands are scaled by 2^24
 // first, which keeps the parts of every normal fp32 value normal bf16 values;
-// sums beyond 2^80, infinities and NaNs make the output non-finite, and such
-// outputs are formed again by plain fp32 sums (repair).
+// sums beyond 2^80, infinities and NaNs make the output non-finite, and a
+// tile with such outputs is computed again for them on the fp32 MFMA.
 //
 // Precision, measured as 2-norm distance from the 64-bit result: 1.5e-7 on
 // the 3x3 C128 N32 layer (fp32 MFMA kernel: 4.3e-7), 1.6e-7 on the 3x3 C512
@@ -212,37 +212,6 @@ split_pack_taps_kernel(const void* __restrict__ SrcV, v4u* __restrict__ Pk, cons
   }
 }
 
-// One output by plain fp32 sums: what IEEE arithmetic gives where infinities
-// or NaNs enter (or sums leave the scaled range).
-template <int NPL>
-__device__ __forceinline__ float repair(const void* InV, const void* KerV, const SplitGeom& g, int n, int k, int h,
-                                        int w) {
-  float acc = 0.f;
-#pragma clang loop unroll(disable)
-  for (int c = 0; c < g.C; ++c)
-#pragma clang loop unroll(disable)
-    for (int r = 0; r < g.R; ++r) {
-      const int y = h * g.sh + r - g.ph;
-#pragma clang loop unroll(disable)
-      for (int s = 0; s < g.S; ++s) {
-        const int x = w * g.sw + s - g.pw;
-        const bool in = (unsigned)y < (unsigned)g.H && (unsigned)x < (unsigned)g.W;
-        const size_t io = in ? (((size_t)n * g.C + c) * g.H + y) * g.W + x : 0;
-        const size_t ko = (((size_t)k * g.C + c) * g.R + r) * g.S + s;
-        float a, b;
-        if constexpr (NPL == 3) {
-          a = static_cast<const float*>(InV)[io];
-          b = static_cast<const float*>(KerV)[ko];
-        } else {
-          a = __builtin_bit_cast(float, (unsigned)static_cast<const unsigned short*>(InV)[io] << 16);
-          b = __builtin_bit_cast(float, (unsigned)static_cast<const unsigned short*>(KerV)[ko] << 16);
-        }
-        acc = __builtin_fmaf(in ? a : 0.f, b, acc);
-      }
-    }
-  return acc;
-}
-
 // ---------------------------------------------------------------------------
 // The convolution.  A workgroup computes BK = 16 WK NWK rows of the packed
 // operand by BP = 16 WP NWP rows of the staged one.  Per chunk of 8 co
@@ -294,19 +263,20 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
   const int nu0 = n0 * g.Hi + (rho0 - n0 * g.P) * g.rm;  // first staged row
 
   // step table: LDS byte offset of each step's unit per lane group (units
-  // past the last tap read tap 0: the packed operand is zero there)
+  // past the last tap read tap 0: the packed operand is zero there), and the
+  // word that says whether a stored output is not finite
   int* tab = reinterpret_cast<int*>(smem + g.tab_off);
-  for (int u = tid; u < 4 * g.steps; u += NT) {
+  for (int u = tid; u <= 4 * g.steps; u += NT) {
     if constexpr (MODE == SPLIT_IMAGE) {
       const int Sp = (g.S + 1) / 2, r = u / Sp, sp = u - r * Sp;
-      tab[u] = r < g.R ? 16 * (r * g.in_wp + sp) : 0;
+      tab[u] = r < g.R ? 16 * (r * g.in_wp + sp) : 0;  // (r >= R for the word)
     } else {
       const int oct = u % g.co;
       int tap = u / g.co;
       if (MODE == SPLIT_POINT || tap >= g.R * g.S) tap = 0;
       const int r = tap / g.S, s = tap - r * g.S;
       const int a = r % g.sh, b = s % g.sw;
-      tab[u] = 16 * (oct * g.Epad + ((a * g.nb + b) * g.in_rows + r / g.sh) * g.in_wp + s / g.sw);
+      tab[u] = u == 4 * g.steps ? 0 : 16 * (oct * g.Epad + ((a * g.nb + b) * g.in_rows + r / g.sh) * g.in_wp + s / g.sw);
     }
   }
 
@@ -317,6 +287,16 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
   unsigned goff[NI], goff2[MODE == SPLIT_IMAGE ? NI : 1], loff[NI];
   unsigned poff[VEC > 1 ? NI : 1][VEC];  // VEC: LDS byte offset of each pixel
   const int HW = g.H * g.W;
+  auto image_item = [&](int it, unsigned& left, unsigned& right, unsigned& slot) {  // (one octet, one phase)
+    const int row = fdiv(it, g.dv_wp), x = it - row * g.in_wp;
+    const int nu = nu0 + row;
+    const int n = fdiv(nu, g.dv_Hi), y = nu - n * g.Hi - g.ph, xx = q0 * g.sw + 2 * x - g.pw;
+    const bool rok = n < g.N && (unsigned)y < (unsigned)g.H;
+    const unsigned base = (unsigned)(ISZ * ((n * g.C * g.H + y) * g.W + xx));
+    slot = 16u * (unsigned)it;
+    left = rok && (unsigned)xx < (unsigned)g.W ? base : kOob;
+    right = rok && (unsigned)(xx + 1) < (unsigned)g.W ? base + ISZ : kOob;
+  };
   if constexpr (VEC > 1) {
     // bf16 layers of one chunk, where single-pixel loads (128 bytes a wave)
     // took most of the time: 32-channel layers with K = 32, 165x136 at batch 9
@@ -373,6 +353,8 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
         loff[i] = 16u * (unsigned)(o * g.Epad + e) | ((unsigned)o << 24);
         const int k = kt * BP + e;
         goff[i] = k < g.K ? 4u * ((unsigned)k * (unsigned)g.C + 8u * (unsigned)o) : kOob;
+      } else if constexpr (MODE == SPLIT_IMAGE) {
+        image_item(it, goff[i], goff2[i], loff[i]);
       } else {
         const int o = fdiv(it, g.dv_E), e = it - o * g.E;
         const int prow = fdiv(e, g.dv_wp), x = e - prow * g.in_wp;
@@ -381,18 +363,10 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
         const int nu = nu0 + row;
         const int n = fdiv(nu, g.dv_Hi), yi = nu - n * g.Hi;
         loff[i] = 16u * (unsigned)(o * g.Epad + e) | ((unsigned)o << 24);
-        if constexpr (MODE == SPLIT_IMAGE) {
-          const int y = yi - g.ph, xx = q0 * g.sw + 2 * x - g.pw;
-          const bool rok = n < g.N && (unsigned)y < (unsigned)g.H;
-          const unsigned base = (unsigned)(ISZ * ((n * g.C * g.H + y) * g.W + xx));
-          goff[i] = rok && (unsigned)xx < (unsigned)g.W ? base : kOob;
-          goff2[i] = rok && (unsigned)(xx + 1) < (unsigned)g.W ? base + ISZ : kOob;
-        } else {
-          const int y = yi * g.sh + a - g.ph, xx = (q0 + x) * g.sw + b - g.pw;
-          goff[i] = n < g.N && (unsigned)y < (unsigned)g.H && (unsigned)xx < (unsigned)g.W
-                        ? (unsigned)(ISZ * (((n * g.C + o * 8) * g.H + y) * g.W + xx))
-                        : kOob;
-        }
+        const int y = yi * g.sh + a - g.ph, xx = (q0 + x) * g.sw + b - g.pw;
+        goff[i] = n < g.N && (unsigned)y < (unsigned)g.H && (unsigned)xx < (unsigned)g.W
+                      ? (unsigned)(ISZ * (((n * g.C + o * 8) * g.H + y) * g.W + xx))
+                      : kOob;
       }
     }
   }
@@ -464,24 +438,27 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
 
   // LDS byte offset of this lane's staged row (output pixel) of each block
   unsigned paddr[WP];
+  auto row_offsets = [&](int j16) {
 #pragma unroll
-  for (int j = 0; j < WP; ++j) {
-    const int p = (wp * WP + j) * 16 + j16;
-    if constexpr (MODE == SPLIT_POINT) {
-      paddr[j] = 16u * (unsigned)p;
-    } else {
-      const int t = fdiv(p, g.dv_tw), col = p - t * g.tw;
-      const int rho = rho0 + t;
-      unsigned ad = 0;
-      if (t < g.tr && rho < rho_end) {
-        const int n = fdiv(rho, g.dv_P);
-        const int row = n * g.Hi + (rho - n * g.P) * g.rm - nu0;
-        ad = MODE == SPLIT_IMAGE ? 16u * (unsigned)(row * g.in_wp) + 8u * (unsigned)(col * g.cm)
-                                 : 16u * (unsigned)(row * g.in_wp + col);
+    for (int j = 0; j < WP; ++j) {
+      const int p = (wp * WP + j) * 16 + j16;
+      if constexpr (MODE == SPLIT_POINT) {
+        paddr[j] = 16u * (unsigned)p;
+      } else {
+        const int t = fdiv(p, g.dv_tw), col = p - t * g.tw;
+        const int rho = rho0 + t;
+        unsigned ad = 0;
+        if (t < g.tr && rho < rho_end) {
+          const int n = fdiv(rho, g.dv_P);
+          const int row = n * g.Hi + (rho - n * g.P) * g.rm - nu0;
+          ad = MODE == SPLIT_IMAGE ? 16u * (unsigned)(row * g.in_wp) + 8u * (unsigned)(col * g.cm)
+                                   : 16u * (unsigned)(row * g.in_wp + col);
+        }
+        paddr[j] = ad;
       }
-      paddr[j] = ad;
     }
-  }
+  };
+  row_offsets(j16);
 
   // packed operand: steps wc, wc + NWC, ... of each chunk
   const int F = g.nchunks * g.steps;
@@ -606,7 +583,8 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
 #pragma unroll
           for (int p = 0; p < NPL; ++p) aq[d][x][p] = aq[d + 1][x][p];
     });
-    if constexpr (!ONE || NWC > 1) __syncthreads();
+    if constexpr (NWC > 1) __syncthreads();
+    else if (!ONE && ch + 1 < g.nchunks) __syncthreads();
   }
   if constexpr (SEP) {
 #pragma unroll
@@ -616,7 +594,7 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
   }
 
   // channel groups: sum in LDS, each group finishing its share of the blocks
-  if constexpr (NWC > 1) {
+  auto sum_groups = [&] {
     float* red = reinterpret_cast<float*>(smem);
     constexpr int RT = WK * WP * 4;
 #pragma unroll
@@ -637,20 +615,21 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
               red + (((q * NWK * NWP + wp * NWK + wk) * (RT / 4) + i * WP + j) * 64 + lane) * 4);
         acc[i][j] = s;
       }
-  }
+  };
+  if constexpr (NWC > 1) sum_groups();
 
   // Block (i, j) holds output channels k0 + 0..3 and one pixel per lane.
   const int PQ = g.P * g.Q;
-  auto locate = [&](int i, int j, int& n, int& h, int& q, int& k0) -> bool {
+  auto locate = [&](int lane16, int i, int j, int& n, int& h, int& q, int& k0) -> bool {
     if constexpr (MODE == SPLIT_POINT) {
-      const int px = rt * BK + (wk * WK + i) * 16 + j16;
+      const int px = rt * BK + (wk * WK + i) * 16 + lane16;
       k0 = kt * BP + (wp * WP + j) * 16 + gq * 4;
       n = fdiv(px, g.dv_PQ);
       h = 0;
       q = px - n * PQ;
       return n < g.N;
     } else {
-      const int p = (wp * WP + j) * 16 + j16;
+      const int p = (wp * WP + j) * 16 + lane16;
       const int t = fdiv(p, g.dv_tw), rho = rho0 + t;
       k0 = kt * BK + (wk * WK + i) * 16 + gq * 4;
       n = fdiv(rho, g.dv_P);
@@ -659,13 +638,15 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
       return t < g.tr && rho < rho_end && q < g.Q;
     }
   };
+  int at16 = j16;  // (IMAGE: opaque, or the offsets of the staged rows would keep their parts for this: spills)
+  if constexpr (MODE == SPLIT_IMAGE) asm volatile("" : "+v"(at16));
   float z = 0.f;  // NaN once a stored output is not finite
 #pragma unroll
   for (int j = 0; j < WP; ++j)
 #pragma unroll
     for (int i = 0; i < WK; ++i) {
       int n, h, q, k0;
-      const bool ok = locate(i, j, n, h, q, k0);
+      const bool ok = locate(at16, i, j, n, h, q, k0);
       if (NWC > 1 && (i * WP + j) % NWC != wc) continue;
       if (!ok) continue;
       OT* o = Out + ((size_t)n * g.K + k0) * PQ + h * g.Q + q;
@@ -677,24 +658,185 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
         o[(size_t)v * PQ] = (OT)(NPL == 3 ? x * kUnscale : x);
       }
     }
-  if (z != z) {
+  if (NPL == 1 && 4 * g.steps == g.co * g.R * g.S) return;  // no unit past the last tap
+  int* nonfinite = reinterpret_cast<int*>(smem + g.tab_off) + 4 * g.steps;
+  if (z != z) *nonfinite = 1;
+  __syncthreads();
+  if (__builtin_expect(__builtin_amdgcn_readfirstlane(*nonfinite) == 0, 1)) return;
+
+  // The tile again, for its outputs that are not finite, as IEEE arithmetic
+  // treats infinities, NaNs and sums beyond the scaled range.  fp32: the
+  // operands themselves on the fp32 MFMA (In is staged with the 8 channels of
+  // a slot as floats in the first two planes), summed per chunk and then over
+  // the chunks.  bf16 operands are multiplied as they are, so only the units
+  // past the last tap can spoil an infinity (it meets a zero there).  These
+  // units are masked in both.  Nothing is pipelined: fp32 tiles take two to
+  // three times their first pass (all of In NaN, 3x3 C128 N32: 49 -> 161 us,
+  // 1x1 C1024 K28269: 112 -> 359 us; each lane summing its outputs by itself,
+  // 3.8 and 37 ms; the tile plans 82 and 284 us).  2-norm error on outputs of
+  // 2^100: 3.1e-7 on C128 and 2.3e-7 on C512 (tile plans 6.1e-7 and 4.3e-7).
+  unsigned bad[(WK * WP * 4 + 31) / 32] = {};
+#pragma unroll
+  for (int b = 0; b < WK * WP * 4; ++b)
+    if (!(__builtin_fabsf(acc[(b >> 2) / WP][(b >> 2) % WP][b & 3]) < __builtin_inff())) bad[b / 32] |= 1u << (b % 32);
+  if constexpr (ONE) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < WK; ++i)
+#pragma unroll
+    for (int j = 0; j < WP; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  // (opaque indices, or parts of the first pass's offsets would be kept in registers for this one)
+  int again = j16, thread = tid, first = 0;
+  asm volatile("" : "+v"(again), "+v"(thread), "+s"(first));
+  row_offsets(again);
+  if constexpr (ONE) __builtin_amdgcn_sched_barrier(0);
+  constexpr bool CHAIN = ONE || NPL == 1;  // (bf16: one chain of sums, as in the first pass)
+  static_assert(!(ONE && NPL == 1) || NWC == 1, "the sums of the groups overwrite the chunk");
+  constexpr bool SERIAL = ONE || NPL == 1;  // an item at a time: fewer registers
+  const auto orsrc = make_rsrc(MODE == SPLIT_POINT ? InV : KerV,
+                               4u * (unsigned)(MODE == SPLIT_POINT ? g.N * g.C * PQ : g.K * g.C * g.R * g.S));
 #pragma clang loop unroll(disable)
-    for (int b = 0; b < WK * WP * 4; ++b) {
-      const int v = b & 3, i = (b >> 2) / WP, j = (b >> 2) - i * WP;
-      int n, h, q, k0;
-      const bool ok = locate(i, j, n, h, q, k0);
-      if (NWC > 1 && (b >> 2) % NWC != wc) continue;
-      const int k = k0 + v;
-      if (!ok || k >= g.K) continue;
-      OT* o = Out + ((size_t)n * g.K + k) * PQ + h * g.Q + q;
-      if (__builtin_fabsf((float)*o) < __builtin_inff()) continue;
-      if constexpr (MODE == SPLIT_POINT) {  // (q runs over the whole image)
-        h = q / g.Q;
-        q -= h * g.Q;
+  for (int ch = first; ch < (ONE ? 1 : g.nchunks); ++ch) {
+    if constexpr (!ONE || NPL == 3) {  // (else the chunk is still in place)
+      __syncthreads();  // (buffer 0 was read)
+      if constexpr (!SERIAL)
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int e = 0; e < LPI; ++e) load_in(i, e, ch);
+      [[maybe_unused]] int it = thread < g.items ? thread : thread % g.items;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        if constexpr (SERIAL) {
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (MODE == SPLIT_IMAGE) {
+            if (i > 0 && it + NT < g.items) it += NT;
+            image_item(it, goff[i], goff2[i], loff[i]);
+          }
+#pragma unroll
+          for (int e = 0; e < LPI; ++e) load_in(i, e, ch);
+        }
+        if constexpr (NPL == 3) {
+          constexpr int M1 = MODE == SPLIT_IMAGE ? 4 : 2, M2 = MODE == SPLIT_IMAGE ? 2 : 4;  // IMAGE: 2 pixels x 2 channels
+          unsigned char* d = smem + (loff[i] & 0xffffffu);
+          *reinterpret_cast<v4u*>(d) = v4u{stg[i][0], stg[i][1], stg[i][M1], stg[i][M1 + 1]};
+          *reinterpret_cast<v4u*>(d + pl_bytes) = v4u{stg[i][M2], stg[i][M2 + 1], stg[i][6], stg[i][7]};
+        } else {
+#pragma unroll
+          for (int q = 0; q < PPI; ++q) convert_piece(i, q, smem);
+        }
       }
-      *o = (OT)repair<NPL>(InV, KerV, g, n, k, h, q);
+      __syncthreads();
     }
+    v4f total[CHAIN ? 1 : WK][CHAIN ? 1 : WP];  // of the chunks before
+    if constexpr (!CHAIN)
+#pragma unroll
+      for (int i = 0; i < WK; ++i)
+#pragma unroll
+        for (int j = 0; j < WP; ++j) total[i][j] = acc[i][j], acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma clang loop unroll(disable)
+    for (int m = wc; m < g.steps; m += NWC) {
+      const int u = 4 * m + gq, off = tab[u];
+      const int Sp = (g.S + 1) / 2;
+      const int tap = MODE == SPLIT_IMAGE ? u / Sp : u / g.co;  // IMAGE: kernel row
+      const int oct = MODE == SPLIT_IMAGE ? 2 * (u - tap * Sp) : u - tap * g.co;  // IMAGE: first column
+      const bool real = tap < (MODE == SPLIT_IMAGE ? g.R : g.R * g.S);
+      if constexpr (NPL == 3) {
+        float a[WK][8];
+#pragma unroll
+        for (int i = 0; i < WK; ++i) {
+          const int row = (MODE == SPLIT_POINT ? rt : kt) * BK + (wk * WK + i) * 16 + j16;
+          const int pn = MODE == SPLIT_POINT ? fdiv(row, g.dv_PQ) : 0;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            bool in;
+            unsigned at;
+            if constexpr (MODE == SPLIT_IMAGE) {
+              const int c = e & 3, s = oct + (e >> 2);
+              in = real && row < g.K && c < g.C && s < g.S;
+              at = (((unsigned)row * g.C + c) * g.R + tap) * g.S + s;
+            } else {
+              const int c = (ch * g.co + oct) * 8 + e;
+              in = real && c < g.C && (MODE == SPLIT_POINT ? pn < g.N : row < g.K);
+              at = MODE == SPLIT_POINT ? ((unsigned)pn * g.C + c) * PQ + (row - pn * PQ)
+                                       : ((unsigned)row * g.C + c) * (g.R * g.S) + tap;
+            }
+            a[i][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(orsrc, in ? 4u * at : kOob, 0, 0));
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < WP; ++j) {
+          const unsigned char* s = smem + paddr[j] + off;
+          float b[8];
+          if constexpr (ONE) __builtin_amdgcn_sched_barrier(0);
+          if constexpr (MODE == SPLIT_IMAGE) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {  // (plane, pixel)
+              const v2u t = *reinterpret_cast<const v2u*>(s + (p >> 1) * pl_bytes + (p & 1) * 8);
+              const bool in = real && ((p & 1) == 0 || oct + 1 < g.S);
+#pragma unroll
+              for (int x = 0; x < 2; ++x) {
+                const unsigned v = in ? t[x] : 0u;
+                b[4 * (p & 1) + 2 * (p >> 1) + x] = __builtin_bit_cast(float, v);
+              }
+            }
+          } else {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+              const v4u t = *reinterpret_cast<const v4u*>(s + p * pl_bytes);
+#pragma unroll
+              for (int x = 0; x < 4; ++x) {
+                const unsigned v = real ? t[x] : 0u;
+                b[4 * p + x] = __builtin_bit_cast(float, v);
+              }
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int i = 0; i < WK; ++i)
+              acc[i][j] = MODE == SPLIT_POINT ? __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[i][e], acc[i][j], 0, 0, 0)
+                                              : __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[e], acc[i][j], 0, 0, 0);
+        }
+      } else {
+        v4u a[WK][NPL], b[NPL];
+#pragma unroll
+        for (int i = 0; i < WK; ++i) load_a(a, i, ch, m);
+#pragma unroll
+        for (int j = 0; j < WP; ++j) {
+          load_b(b, smem, paddr[j] + off);
+#pragma unroll
+          for (int x = 0; x < 4; ++x) b[0][x] = real ? b[0][x] : 0u;
+#pragma unroll
+          for (int i = 0; i < WK; ++i) mma1(a[i][0], b[0], acc[i][j]);
+        }
+      }
+    }
+    if constexpr (!CHAIN)
+#pragma unroll
+      for (int i = 0; i < WK; ++i)
+#pragma unroll
+        for (int j = 0; j < WP; ++j) acc[i][j] += total[i][j];
   }
+  if constexpr (NWC > 1) {
+    __syncthreads();
+    sum_groups();
+  }
+  asm volatile("" : "+v"(again));
+#pragma unroll
+  for (int j = 0; j < WP; ++j)
+#pragma unroll
+    for (int i = 0; i < WK; ++i) {
+      int n, h, q, k0;
+      const bool ok = locate(again, i, j, n, h, q, k0);
+      if (NWC > 1 && (i * WP + j) % NWC != wc) continue;
+      if (!ok) continue;
+      OT* o = Out + ((size_t)n * g.K + k0) * PQ + h * g.Q + q;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int b = (i * WP + j) * 4 + v;
+        if (k0 + v < g.K && (bad[b / 32] >> (b % 32) & 1)) o[(size_t)v * PQ] = (OT)acc[i][j][v];
+      }
+    }
 }
 
 typedef void (*SplitFnF)(const void*, const v4u*, const void*, float*, SplitGeom);

@@ -107,7 +107,7 @@ bool split_geometry(const SplitShape& s, const SplitConfig& c, int tr, int tw, i
   const int stage = (c.one ? 1 : 2) * g.buf_bytes;
   const int red = c.nwc > 1 ? NT / 64 * c.wk * c.wp * 1024 : 0;
   g.tab_off = std::max(stage, red);
-  const int lds = g.tab_off + 16 * g.steps;
+  const int lds = g.tab_off + 16 * g.steps + 16;  // (a word for the non-finite flag)
   if (lds > kLds) return false;
   if (c.mode == SPLIT_CONV && 4 * 16 * (8 * s.R * s.S + 1) * e > 65536) return false;  // packing kernel's LDS
   g.dv_E = make_fastdiv(c.vec > 1 ? g.E4 : g.E);
