@@ -35,6 +35,13 @@
  * which is safe only once the old stream's work has finished.  A call that
  * finds its buffer held by another host thread takes and returns a fresh one
  * in stream order.  conv_fwd_ex_noalloc allocates nothing (see there).
+ * Graph capture: a captured call records the address of the workspaces kept
+ * for its stream.  They stay allocated until conv_fwd_release_workspaces, also
+ * when a later call on the stream needs larger ones, so graphs may be replayed
+ * after any eager calls, but in order with these calls and with one another,
+ * and not after the release.  A captured call that needs more than is kept
+ * allocates and frees it within the graph; call the layer once on the stream
+ * before the capture to avoid that.
  * The calling thread's current device must own the stream.
  * In, Ker and Out must not overlap.
  *

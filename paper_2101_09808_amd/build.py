@@ -13,10 +13,12 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libconvfwd.so")
 INCLUDE = os.path.join(os.path.dirname(PKG), "include")
 
-SOURCES = ("conv_kernels.hip", "split_kernels.hip", "conv_api.cpp", "select.cpp", "split_route.cpp")
+SOURCES = ("conv_kernels.hip", "split_kernels.hip", "conv_api.cpp", "select.cpp", "split_route.cpp", "workspace.cpp")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
+# host sources call the HIP runtime (hipcc adds its headers to device sources only)
+HOST_FLAGS = ["-D__HIP_PLATFORM_AMD__", "-I", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include")]
 # Packed fp32 instructions are disabled for all device code.
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I", INCLUDE, "-I", CSRC,
@@ -27,7 +29,7 @@ def _compile(src):
     out = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
     cmd = [HIPCC, *COMMON, *DEVICE_FLAGS, "-c", os.path.join(CSRC, src), "-o", out]
     if src.endswith(".cpp"):
-        cmd = [HIPCC, *COMMON, "-x", "c++", "-c", os.path.join(CSRC, src), "-o", out]
+        cmd = [HIPCC, *COMMON, *HOST_FLAGS, "-x", "c++", "-c", os.path.join(CSRC, src), "-o", out]
     r = subprocess.run(cmd, capture_output=True, text=True)
     msgs = [ln for ln in (r.stdout + r.stderr).splitlines() if "packed-fp32-ops" not in ln]
     if r.returncode != 0:

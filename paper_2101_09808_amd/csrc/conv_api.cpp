@@ -506,7 +506,7 @@ int ex_need(const PhaseGeom& p, int dtype, const void* In, const void* Ker, Need
 // called the layer on this stream before captures no allocation.
 void reserve_planned(int st, const Need& need, void* stream) {
   for (int l = 0; st == CONV_OK && l < 3; ++l)
-    if (need.level[l] > 0) st = workspace_reserve(l, need.level[l], stream);
+    if (need.level[l] > 0) workspace_reserve(l, need.level[l], stream);
 }
 
 int run_selected(const Shape& s, int dtype, const void* In, const void* Ker, float* Out, void* stream) {

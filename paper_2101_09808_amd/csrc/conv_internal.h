@@ -135,6 +135,7 @@ struct PhaseGeom {
 bool phase_direct(const Variant& v, const PhaseGeom& p, int dtype, Geom* g);
 // Stream-ordered device memory from the library's per-device pool
 // (hipMallocFromPoolAsync / hipFreeAsync on `stream`).
+constexpr int kMaxDevices = 64;
 int stream_alloc(size_t bytes, void* stream, void** out);
 int stream_free(void* p, void* stream);
 // A call's workspace: the buffer the library keeps for (current device,
@@ -151,9 +152,11 @@ struct Workspace {
 };
 int workspace_acquire(int level, size_t bytes, void* stream, Workspace* w);
 int workspace_release(const Workspace& w, void* stream);
+// Is the stream being captured into a graph (or can that not be told)?
+bool stream_capturing(void* stream);
 // Grows the buffer kept for the stream and level to at least `bytes` unless
-// another host thread holds it.
-int workspace_reserve(int level, size_t bytes, void* stream);
+// another host thread holds it or there is no room (it is left as it is then).
+void workspace_reserve(int level, size_t bytes, void* stream);
 // Frees (stream-ordered) the buffers kept for `stream` on the current device.
 int workspace_release_stream(void* stream);
 // Allocation-free calls: while an arena is installed on the calling thread,

@@ -25,9 +25,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <map>
 #include <mutex>
-#include <tuple>
 #include <type_traits>
 #include <utility>
 #include <vector>
@@ -2193,41 +2191,6 @@ int allow_dynamic_lds(const void* fn) {
                                                                                                   : CONV_EHIP;
 }
 
-// Workspaces come from a memory pool the library owns, one per device,
-// which keeps up to 1 GB of freed blocks for reuse (the default pool hands
-// freed memory back at each synchronisation, so every call would map fresh
-// pages).  The calling thread's current device must own the stream.
-constexpr int kMaxDevices = 64;
-
-int stream_alloc(size_t bytes, void* stream, void** out) {
-  static std::mutex mu;
-  static hipMemPool_t pools[kMaxDevices] = {};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return CONV_EHIP;
-  hipMemPool_t pool = nullptr;
-  {
-    std::lock_guard<std::mutex> lk(mu);
-    if (!pools[dev]) {
-      hipMemPoolProps props = {};
-      props.allocType = hipMemAllocationTypePinned;
-      props.location.type = hipMemLocationTypeDevice;
-      props.location.id = dev;
-      hipMemPool_t p = nullptr;
-      if (hipMemPoolCreate(&p, &props) != hipSuccess) return CONV_EHIP;
-      uint64_t keep = uint64_t(1) << 30;
-      if (hipMemPoolSetAttribute(p, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) return CONV_EHIP;
-      pools[dev] = p;
-    }
-    pool = pools[dev];
-  }
-  return hipMallocFromPoolAsync(out, bytes, pool, reinterpret_cast<hipStream_t>(stream)) == hipSuccess ? CONV_OK
-                                                                                                      : CONV_EHIP;
-}
-
-int stream_free(void* p, void* stream) {
-  return hipFreeAsync(p, reinterpret_cast<hipStream_t>(stream)) == hipSuccess ? CONV_OK : CONV_EHIP;
-}
-
 // ---------------------------------------------------------------------------
 // Scratch of the allocation-free entry point: a static device array.  Every
 // GPU that loads the library's code object holds its own copy (at its own
@@ -2250,100 +2213,6 @@ int noalloc_scratch(void** base) {
   }
   *base = addr[dev];
   return CONV_OK;
-}
-
-namespace {
-// Workspaces kept per (device, stream, nesting level): the kernels of the
-// calls on one stream run in stream order, so a call can reuse the buffer
-// the previous call on that stream used.  A buffer grows by a stream-ordered
-// free and a new allocation; while another host thread holds it, a call
-// takes a fresh stream-ordered allocation instead.
-struct CachedWorkspace {
-  void* ptr = nullptr;
-  size_t size = 0;
-  bool busy = false;
-};
-std::mutex g_ws_mu;
-std::map<std::tuple<int, void*, int>, CachedWorkspace> g_ws;
-
-// The arena of the calling thread's allocation-free call, if one is running.
-thread_local ScratchArena* t_arena = nullptr;
-}  // namespace
-
-void set_thread_arena(ScratchArena* a) { t_arena = a; }
-
-static int grow_kept(CachedWorkspace& c, size_t bytes, void* stream) {
-  if (c.size >= bytes) return CONV_OK;
-  if (c.ptr && stream_free(c.ptr, stream) != CONV_OK) return CONV_EHIP;
-  c.ptr = nullptr;
-  c.size = 0;
-  const size_t sz = (bytes + (size_t(1) << 20) - 1) >> 20 << 20;  // whole MiB
-  if (stream_alloc(sz, stream, &c.ptr) != CONV_OK) return CONV_EHIP;
-  c.size = sz;
-  return CONV_OK;
-}
-
-int workspace_reserve(int level, size_t bytes, void* stream) {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return CONV_EHIP;
-  std::lock_guard<std::mutex> lk(g_ws_mu);
-  CachedWorkspace& c = g_ws[std::make_tuple(dev, stream, level)];
-  return c.busy ? CONV_OK : grow_kept(c, bytes, stream);
-}
-
-int workspace_acquire(int level, size_t bytes, void* stream, Workspace* w) {
-  w->cached = false;
-  w->arena = false;
-  w->level = level;
-  if (t_arena) {
-    // bump allocation from the caller's scratch, 256-byte aligned
-    const size_t off = (t_arena->used + 255) / 256 * 256;
-    if (off > t_arena->cap || bytes > t_arena->cap - off) return CONV_ESCRATCH;
-    w->ptr = t_arena->base + off;
-    w->arena = true;
-    t_arena->used = off + bytes;
-    return CONV_OK;
-  }
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return CONV_EHIP;
-  {
-    std::lock_guard<std::mutex> lk(g_ws_mu);
-    CachedWorkspace& c = g_ws[std::make_tuple(dev, stream, level)];
-    if (!c.busy) {
-      if (grow_kept(c, bytes, stream) != CONV_OK) return CONV_EHIP;
-      c.busy = true;
-      w->ptr = c.ptr;
-      w->cached = true;
-      return CONV_OK;
-    }
-  }
-  return stream_alloc(bytes, stream, &w->ptr);
-}
-
-int workspace_release(const Workspace& w, void* stream) {
-  if (w.arena) return CONV_OK;
-  if (!w.cached) return stream_free(w.ptr, stream);
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return CONV_EHIP;
-  std::lock_guard<std::mutex> lk(g_ws_mu);
-  g_ws[std::make_tuple(dev, stream, w.level)].busy = false;
-  return CONV_OK;
-}
-
-int workspace_release_stream(void* stream) {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return CONV_EHIP;
-  std::lock_guard<std::mutex> lk(g_ws_mu);
-  int rc = CONV_OK;
-  for (auto it = g_ws.begin(); it != g_ws.end();) {
-    if (std::get<0>(it->first) == dev && std::get<1>(it->first) == stream && !it->second.busy) {
-      if (it->second.ptr && stream_free(it->second.ptr, stream) != CONV_OK) rc = CONV_EHIP;
-      it = g_ws.erase(it);
-    } else {
-      ++it;
-    }
-  }
-  return rc;
 }
 
 int launch_phase_split(const PhaseGeom& p, int dtype, const void* In, const void* Ker, void* Inp, void* Kp,

@@ -77,7 +77,4 @@ bool split_choose(const SplitShape& s, SplitPlan* p);
 // Enqueues the packing and the convolution; Pk has p.pk_bytes bytes.
 int split_launch(const SplitPlan& p, bool out_bf16, const void* In, const void* Ker, void* Pk, void* Out, void* stream);
 
-// Is the stream being captured into a graph (or can that not be told)?
-bool stream_capturing(void* stream);
-
 }  // namespace convfwd

@@ -873,15 +873,6 @@ const SplitConfig* split_configs(int* count) {
   return table;
 }
 
-bool stream_capturing(void* stream) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(reinterpret_cast<hipStream_t>(stream), &cs) != hipSuccess) {
-    (void)hipGetLastError();  // (not this call's error to report)
-    return true;
-  }
-  return cs != hipStreamCaptureStatusNone;
-}
-
 int split_launch(const SplitPlan& p, bool out_bf16, const void* In, const void* Ker, void* Pk, void* Out,
                  void* stream) {
   const SplitInstance* inst = nullptr;

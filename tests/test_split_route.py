@@ -556,6 +556,42 @@ def test_capture_of_a_layer_whose_plan_needs_workspaces(s, bf16_out):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("called_before", [True, False])
+def test_a_captured_layer_outlives_a_larger_call(called_before):
+    """Replays of a captured layer whose plan needs a workspace give the eager
+    result after a larger layer has run on the stream, whether the layer's own
+    workspace was kept at the capture or the graph allocates it."""
+    s = ConvShape("sp_cap_small", 4, 64, 128, 28, 28, 3, 3, "bf16", 771, 2, 1)
+    big = ConvShape("sp_cap_larger", 8, 64, 128, 60, 60, 3, 3, "bf16", 772, 2, 1)
+    In, Ker = make_inputs(s)
+    In_d, Ker_d = In.to(DEV), Ker.to(DEV)
+    ref = oracle(s, In, Ker)
+    bIn, bKer = (x.to(DEV) for x in make_inputs(big))
+    st = torch.cuda.Stream()
+    out = torch.zeros(s.N, s.K, s.P, s.Q, device=DEV)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(st):
+        if called_before:
+            B.conv_fwd_ex(In_d, Ker_d, s.stride, s.pad, out=out)
+    st.synchronize()
+    say(f"[gpu] capture {s.name} called_before={called_before}")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        B.conv_fwd_ex(In_d, Ker_d, s.stride, s.pad, out=out)
+    for _ in range(3):
+        with torch.cuda.stream(st):
+            B.conv_fwd_ex(bIn, bKer, big.stride, big.pad)
+        torch.cuda.synchronize()
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.max(np.abs(out.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref))
+    del graph
+    torch.cuda.synchronize()
+    B.release_workspaces(st)
+
+
+@pytest.mark.gpu
 def test_tuned_layer_keeps_the_faster_route():
     s = ConvShape("sp_tuned", 4, 128, 128, 30, 30, 3, 3, "f32", 751)
     In, Ker = make_inputs(s)
