@@ -405,7 +405,8 @@ int conv_fwd_ex_plan(int N, int C, int K, int H, int W, int R, int S, int stride
 
 /*
  * Host only: does this layer run on the split-operand kernels instead of its
- * tile plan, and how?  Those kernels form the sums on the bf16 MFMAs: fp32
+ * tile plan, and how?  (For 16-byte aligned tensors; a layer whose plan
+ * conv_fwd_tune found faster is reported on its plan from then on.)  Those kernels form the sums on the bf16 MFMAs: fp32
  * operands are split exactly into three bf16 parts each, of whose nine
  * products the six that matter at fp32 precision are summed in fp32 (measured
  * closer to the 64-bit result than the fp32 MFMA kernels); bf16 operands are

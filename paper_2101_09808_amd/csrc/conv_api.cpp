@@ -97,11 +97,8 @@ int cached_entry(const Shape& s, int dtype, int align, Entry* out) {
   Entry e;
   const int st = select_entry(s, dtype, align, &e);
   if (st != CONV_OK) return st;
-  {
-    std::lock_guard<std::mutex> lk(g_mu);
-    g_cache[key] = e;
-  }
-  *out = e;
+  std::lock_guard<std::mutex> lk(g_mu);
+  *out = g_cache.emplace(key, e).first->second;  // (another thread may have tuned the layer meanwhile)
   return CONV_OK;
 }
 
@@ -409,7 +406,9 @@ int routed_entry(const Shape& s, int dtype, int align, Entry* e) {
   e->split = split_route(split_shape(s.N, s.C, s.K, s.H, s.W, s.R, s.S, 1, 1, 0, 0, dtype), align);
   if (st != CONV_OK) return st;
   std::lock_guard<std::mutex> lk(g_mu);
-  g_cache[Key{s.N, s.C, s.K, s.H, s.W, s.R, s.S, dtype, align}].split = e->split;
+  Entry& kept = g_cache[Key{s.N, s.C, s.K, s.H, s.W, s.R, s.S, dtype, align}];
+  if (kept.split < 0) kept.split = e->split;
+  e->split = kept.split;  // (conv_fwd_tune on another thread may have decided meanwhile)
   return CONV_OK;
 }
 
@@ -926,7 +925,13 @@ int conv_fwd_split_plan(int N, int C, int K, int H, int W, int R, int S, int str
   if (cap > 0 && !out) return CONV_ENULL;
   if (dtype != CONV_DTYPE_F32 && dtype != CONV_DTYPE_BF16) return CONV_EINVAL;
   const SplitShape q = split_shape(N, C, K, H, W, R, S, stride_h, stride_w, pad_h, pad_w, dtype);
-  const SplitEntry e = split_entry(q);
+  SplitEntry e = split_entry(q);
+  if (stride_h == 1 && stride_w == 1 && pad_h == 0 && pad_w == 0) {
+    // conv_fwd_tune may have found the plan faster
+    std::lock_guard<std::mutex> lk(g_mu);
+    const auto it = g_cache.find(Key{N, C, K, H, W, R, S, dtype, ALIGN_ALL});
+    if (it != g_cache.end() && it->second.split == 0) e.use = false;
+  }
   int32_t f[CONV_SPLIT_FIELDS] = {0};
   if (e.use) {
     const SplitConfig& c = *e.p.cfg;

@@ -592,16 +592,28 @@ def test_a_captured_layer_outlives_a_larger_call(called_before):
 
 
 @pytest.mark.gpu
-def test_tuned_layer_keeps_the_faster_route():
-    s = ConvShape("sp_tuned", 4, 128, 128, 30, 30, 3, 3, "f32", 751)
+@pytest.mark.parametrize("dims", [(4, 128, 128, 30, 30, 3, 3), (1, 43, 64, 16, 16, 3, 3), (2, 64, 96, 40, 40, 1, 1)],
+                         ids=str)
+def test_tuned_layer_keeps_the_faster_route(dims):
+    """After tuning, calls give the bits of the route that conv_fwd_split_plan
+    reports: the split kernels', or the tuned plan's."""
+    s = ConvShape("sp_tuned", *dims, "f32", 751)
     In, Ker = make_inputs(s)
     In_d, Ker_d = In.to(DEV), Ker.to(DEV)
     ref = oracle(s, In, Ker)
-    out, plan, _ = B.conv_fwd_tune(In_d, Ker_d, top_n=3, reps=3)
-    torch.cuda.synchronize()
-    assert np.max(np.abs(out.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref))
+    before = split_plan(s)
+    first = B.conv_fwd(In_d, Ker_d)
+    say(f"[gpu] tune {dims}")
+    out, plan, _ = B.conv_fwd_tune(In_d, Ker_d, top_n=24, reps=5)
     planned = B.conv_fwd_with_plan(In_d, Ker_d, plan)
     again = B.conv_fwd(In_d, Ker_d)
     torch.cuda.synchronize()
-    assert np.max(np.abs(again.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref))
-    assert split_plan(s) is not None or torch.equal(again, planned)
+    for x in (out, planned, again):
+        assert np.max(np.abs(x.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref))
+    after = split_plan(s)
+    say(f"[gpu] tuned {dims}: split before {bool(before)} after {bool(after)}")
+    if before is None:
+        assert after is None
+    else:
+        assert not torch.equal(first, planned), "the routes give the same bits: nothing is told apart"
+    assert torch.equal(again, first if after else planned)
