@@ -31,7 +31,7 @@ int validate_shape(int N, int C, int K, int H, int W, int R, int S) {
 // Per (shape, dtype, tensor alignment) the selected plan and its resolved launch.
 struct Entry {
   conv_plan_t plan;
-  const Variant* v;
+  const Variant* v = nullptr;  // none: no plan takes the shape (that is cached too)
   Geom g;
   int split = -1;  // the call takes the split-operand route: 1 yes, 0 no, -1 not looked up yet
 };
@@ -91,15 +91,16 @@ int cached_entry(const Shape& s, int dtype, int align, Entry* out) {
     auto it = g_cache.find(key);
     if (it != g_cache.end()) {
       *out = it->second;
-      return CONV_OK;
+      return out->v ? CONV_OK : CONV_ENOPLAN;
     }
   }
   Entry e;
   const int st = select_entry(s, dtype, align, &e);
-  if (st != CONV_OK) return st;
+  if (st != CONV_OK && st != CONV_ENOPLAN) return st;
+  if (st != CONV_OK) e.v = nullptr;
   std::lock_guard<std::mutex> lk(g_mu);
   *out = g_cache.emplace(key, e).first->second;  // (another thread may have tuned the layer meanwhile)
-  return CONV_OK;
+  return out->v ? CONV_OK : CONV_ENOPLAN;
 }
 
 // bf16 Out from the transposing bf16 kernel: its stores are 16 bytes only
@@ -295,6 +296,85 @@ int phase_geom(int N, int C, int K, int H, int W, int R, int S, int sh, int sw, 
   return CONV_OK;
 }
 
+// Workspaces that the planned route takes for a call: their bytes summed, each
+// rounded up to the 256-byte alignment of the arena's bump allocation, and
+// the bytes of each level's kept buffer (a level's second workspace in one
+// call is a fresh allocation).  Mirrors the dispatch of run_ex, run_planned,
+// run_bf16_widened, launch (split partial sums) and launch_bf16_out; any
+// workspace the library carves is 256-byte aligned, which is what the
+// alignment of the plans that run on workspaces is computed with.
+size_t up256(size_t b) { return (b + 255) / 256 * 256; }
+
+struct Need {
+  size_t total = 0;
+  size_t level[3] = {0, 0, 0};
+  void add(int l, size_t bytes) {
+    total += up256(bytes);
+    if (level[l] == 0) level[l] = bytes;
+  }
+  void add_split(const Geom& g) {
+    if (g.split > 1) add(2, (size_t)g.split * g.N * g.K * g.P * g.Q * sizeof(float));
+  }
+};
+
+// run_bf16_widened: exact fp32 copies of In and Ker (and for bf16 Out the
+// fp32 one), then the fp32 plan
+int widened_need(const Shape& s, bool out_bf16, Need* need) {
+  const size_t n_in = (size_t)s.N * s.C * s.H * s.W, n_ker = (size_t)s.K * s.C * s.R * s.S;
+  const size_t n_out = out_bf16 ? (size_t)s.N * s.K * (s.H - s.R + 1) * (s.W - s.S + 1) : 0;
+  Entry e;
+  const int st = cached_entry(s, CONV_DTYPE_F32, ALIGN_ALL, &e);
+  if (st != CONV_OK) return st;
+  need->add(0, up256(n_in * 4) + up256(n_ker * 4) + n_out * 4);
+  need->add_split(e.g);
+  return CONV_OK;
+}
+
+int selected_need(const Shape& s, int dtype, int align, Need* need) {
+  Entry e;
+  const int st = cached_entry(s, dtype, align, &e);
+  if (st == CONV_ENOPLAN && dtype == CONV_DTYPE_BF16) return widened_need(s, false, need);
+  if (st == CONV_OK) need->add_split(e.g);
+  return st;
+}
+
+int bf16_out_need(const Shape& s, int align, bool pair_possible, Need* need) {
+  Entry e;
+  const int st = cached_entry_bf16_out(s, align, pair_possible, &e);
+  if (st == CONV_ENOPLAN) return widened_need(s, true, need);
+  if (st != CONV_OK) return st;
+  if (bf16_out_staged(*e.v)) {
+    need->add(1, (size_t)e.g.N * e.g.K * e.g.P * e.g.Q * sizeof(float));
+    need->add_split(e.g);
+  }
+  return CONV_OK;
+}
+
+int ex_need(const PhaseGeom& p, int dtype, int align, Need* need) {
+  const Shape s{p.N, p.C, p.K, p.H, p.W, p.R, p.S};
+  if (p.sh == 1 && p.sw == 1 && p.ph == 0 && p.pw == 0) return selected_need(s, dtype, align, need);
+  const size_t e = dtype == CONV_DTYPE_BF16 ? 2 : 4;
+  const int Cp = p.C * p.na * p.nb;
+  const bool ker_moves = p.na * p.nb > 1;
+  const Shape inner{p.N, Cp, p.K, p.Hp, p.Wp, p.Rp, p.Sp};
+  // the plan runs on (aligned) phase images and the rearranged or the
+  // caller's Ker
+  const int ker_al = ker_moves ? ALIGN_KER : (align & ALIGN_KER);
+  const int al_split = ALIGN_IN | ALIGN_IN4 | ker_al;
+  const size_t ker_ws = ker_moves ? (size_t)p.K * Cp * p.Rp * p.Sp * e : 0;
+  const size_t in_ws = up256((size_t)p.N * Cp * p.Hp * p.Wp * e);
+  if (dtype == CONV_DTYPE_F32) {
+    ExEntry x;
+    const int st = cached_ex_entry(p, (align & (ALIGN_IN | ALIGN_IN4)) | ker_al, al_split, &x);
+    if (st != CONV_OK) return st;
+    need->add(0, (x.direct ? 0 : in_ws) + ker_ws);
+    need->add_split(x.e.g);
+    return CONV_OK;
+  }
+  need->add(0, in_ws + ker_ws);
+  return selected_need(inner, dtype, al_split, need);
+}
+
 // ---------------------------------------------------------------------------
 // Split-operand route: layers that the kernels of split_kernels.hip run
 // faster than the tile plan.  The two are compared by their estimates: the
@@ -302,8 +382,11 @@ int phase_geom(int N, int C, int K, int H, int W, int R, int S, int sh, int sw, 
 // plan's (split_choose).  The choice depends on the layer alone, not on the
 // type of Out, so bf16 Out stays the rounded fp32 Out.
 struct SplitEntry {
-  bool use;
+  bool use = false;
   SplitPlan p;
+  // what the planned route keeps for 16-byte aligned tensors; bf16 Out
+  // without and with 16-byte stores
+  Need need, out_need[2];
 };
 typedef std::tuple<int, int, int, int, int, int, int, int, int, int, int> SplitKey;
 std::map<SplitKey, SplitEntry> g_split_cache;
@@ -363,7 +446,6 @@ SplitEntry split_entry(const SplitShape& s) {
     if (it != g_split_cache.end()) return it->second;
   }
   SplitEntry e;
-  std::memset(&e, 0, sizeof(e));
   double us = 0;
   // The packed operand also has to fit the allocation-free entry point's
   // scratch, so that it takes the same route.
@@ -377,6 +459,13 @@ SplitEntry split_entry(const SplitShape& s) {
   e.use = planned_time(s, &us) == CONV_OK && split_choose(s, &e.p) &&
           e.p.pk_bytes <= (size_t)CONV_NOALLOC_SCRATCH_BYTES &&
           e.p.us < (s.dtype == CONV_DTYPE_F32 && us < 26 ? 0.88 : e.p.g.num_tiles >= 128 ? 0.97 : 0.9) * us;
+  PhaseGeom p;
+  if (e.use && phase_geom(s.N, s.C, s.K, s.H, s.W, s.R, s.S, s.sh, s.sw, s.ph, s.pw, &p) == CONV_OK) {
+    (void)ex_need(p, s.dtype, ALIGN_ALL, &e.need);
+    if (s.dtype == CONV_DTYPE_BF16 && s.sh == 1 && s.sw == 1 && s.ph == 0 && s.pw == 0)
+      for (int pair = 0; pair < 2; ++pair)
+        (void)bf16_out_need(Shape{s.N, s.C, s.K, s.H, s.W, s.R, s.S}, ALIGN_ALL, pair != 0, &e.out_need[pair]);
+  }
   std::lock_guard<std::mutex> lk(g_mu);
   g_split_cache[key] = e;
   return e;
@@ -402,14 +491,14 @@ bool takes_split(const Entry& e, void* stream, bool static_scratch) {
 // has a route too (its planned one widens the inputs).
 int routed_entry(const Shape& s, int dtype, int align, Entry* e) {
   const int st = cached_entry(s, dtype, align, e);
-  if (st == CONV_OK ? e->split >= 0 : st != CONV_ENOPLAN || dtype != CONV_DTYPE_BF16) return st;
+  if (st != CONV_OK && (st != CONV_ENOPLAN || dtype != CONV_DTYPE_BF16)) return st;
+  if (e->split >= 0) return st;
   e->split = split_route(split_shape(s.N, s.C, s.K, s.H, s.W, s.R, s.S, 1, 1, 0, 0, dtype), align);
-  if (st != CONV_OK) return st;
   std::lock_guard<std::mutex> lk(g_mu);
   Entry& kept = g_cache[Key{s.N, s.C, s.K, s.H, s.W, s.R, s.S, dtype, align}];
   if (kept.split < 0) kept.split = e->split;
   e->split = kept.split;  // (conv_fwd_tune on another thread may have decided meanwhile)
-  return CONV_OK;
+  return st;
 }
 
 int run_split(const SplitEntry& e, bool out_bf16, const void* In, const void* Ker, void* Out, void* stream) {
@@ -421,101 +510,22 @@ int run_split(const SplitEntry& e, bool out_bf16, const void* In, const void* Ke
   return st == CONV_OK ? freed : st;
 }
 
-// Workspaces that the planned route takes for a call: their bytes summed, each
-// rounded up to the 256-byte alignment of the arena's bump allocation, and
-// the bytes of each level's kept buffer (a level's second workspace in one
-// call is a fresh allocation).  Mirrors the dispatch of run_ex, run_planned,
-// run_bf16_widened, launch (split partial sums) and launch_bf16_out; any
-// workspace the library carves is 256-byte aligned, which is what the
-// alignment of the plans that run on workspaces is computed with.
-size_t up256(size_t b) { return (b + 255) / 256 * 256; }
-
-struct Need {
-  size_t total = 0;
-  size_t level[3] = {0, 0, 0};
-  void add(int l, size_t bytes) {
-    total += up256(bytes);
-    if (level[l] == 0) level[l] = bytes;
-  }
-  void add_split(const Geom& g) {
-    if (g.split > 1) add(2, (size_t)g.split * g.N * g.K * g.P * g.Q * sizeof(float));
-  }
-};
-
-// run_bf16_widened: exact fp32 copies of In and Ker (and for bf16 Out the
-// fp32 one), then the fp32 plan
-int widened_need(const Shape& s, bool out_bf16, Need* need) {
-  const size_t n_in = (size_t)s.N * s.C * s.H * s.W, n_ker = (size_t)s.K * s.C * s.R * s.S;
-  const size_t n_out = out_bf16 ? (size_t)s.N * s.K * (s.H - s.R + 1) * (s.W - s.S + 1) : 0;
-  Entry e;
-  const int st = cached_entry(s, CONV_DTYPE_F32, ALIGN_ALL, &e);
-  if (st != CONV_OK) return st;
-  need->add(0, up256(n_in * 4) + up256(n_ker * 4) + n_out * 4);
-  need->add_split(e.g);
-  return CONV_OK;
-}
-
-int selected_need(const Shape& s, int dtype, int align, Need* need) {
-  Entry e;
-  const int st = cached_entry(s, dtype, align, &e);
-  if (st == CONV_ENOPLAN && dtype == CONV_DTYPE_BF16) return widened_need(s, false, need);
-  if (st == CONV_OK) need->add_split(e.g);
-  return st;
-}
-
-int bf16_out_need(const Shape& s, int align, bool pair_possible, Need* need) {
-  Entry e;
-  const int st = cached_entry_bf16_out(s, align, pair_possible, &e);
-  if (st == CONV_ENOPLAN) return widened_need(s, true, need);
-  if (st != CONV_OK) return st;
-  if (bf16_out_staged(*e.v)) {
-    need->add(1, (size_t)e.g.N * e.g.K * e.g.P * e.g.Q * sizeof(float));
-    need->add_split(e.g);
-  }
-  return CONV_OK;
-}
-
-int ex_need(const PhaseGeom& p, int dtype, const void* In, const void* Ker, Need* need) {
-  const Shape s{p.N, p.C, p.K, p.H, p.W, p.R, p.S};
-  if (p.sh == 1 && p.sw == 1 && p.ph == 0 && p.pw == 0) return selected_need(s, dtype, alignment_of(In, Ker), need);
-  const size_t e = dtype == CONV_DTYPE_BF16 ? 2 : 4;
-  const int Cp = p.C * p.na * p.nb;
-  const bool ker_moves = p.na * p.nb > 1;
-  const Shape inner{p.N, Cp, p.K, p.Hp, p.Wp, p.Rp, p.Sp};
-  // the plan runs on (aligned) phase images and the rearranged or the
-  // caller's Ker
-  const int ker_al = ker_moves ? ALIGN_KER : (alignment_of(In, Ker) & ALIGN_KER);
-  const int al_split = ALIGN_IN | ALIGN_IN4 | ker_al;
-  const size_t ker_ws = ker_moves ? (size_t)p.K * Cp * p.Rp * p.Sp * e : 0;
-  const size_t in_ws = up256((size_t)p.N * Cp * p.Hp * p.Wp * e);
-  if (dtype == CONV_DTYPE_F32) {
-    ExEntry x;
-    const int st = cached_ex_entry(p, (alignment_of(In, Ker) & (ALIGN_IN | ALIGN_IN4)) | ker_al, al_split, &x);
-    if (st != CONV_OK) return st;
-    need->add(0, (x.direct ? 0 : in_ws) + ker_ws);
-    need->add_split(x.e.g);
-    return CONV_OK;
-  }
-  need->add(0, in_ws + ker_ws);
-  return selected_need(inner, dtype, al_split, need);
-}
-
 // A call on the split-operand route keeps the buffers of its planned route
 // too: under graph capture the same call runs that, and a program that has
 // called the layer on this stream before captures no allocation.
-void reserve_planned(int st, const Need& need, void* stream) {
-  for (int l = 0; st == CONV_OK && l < 3; ++l)
+void reserve_planned(const Need& need, void* stream) {
+  for (int l = 0; l < 3; ++l)
     if (need.level[l] > 0) workspace_reserve(l, need.level[l], stream);
 }
 
 int run_selected(const Shape& s, int dtype, const void* In, const void* Ker, float* Out, void* stream) {
   Entry e;
-  const int st = routed_entry(s, dtype, alignment_of(In, Ker), &e);
+  const int align = alignment_of(In, Ker), st = routed_entry(s, dtype, align, &e);
   if (takes_split(e, stream, false)) {
-    Need need;
-    reserve_planned(selected_need(s, dtype, alignment_of(In, Ker), &need), need, stream);
-    return run_split(split_entry(split_shape(s.N, s.C, s.K, s.H, s.W, s.R, s.S, 1, 1, 0, 0, dtype)), false, In, Ker, Out,
-                     stream);
+    SplitEntry se = split_entry(split_shape(s.N, s.C, s.K, s.H, s.W, s.R, s.S, 1, 1, 0, 0, dtype));
+    if (align != ALIGN_ALL) (void)selected_need(s, dtype, align, &(se.need = Need()));
+    reserve_planned(se.need, stream);
+    return run_split(se, false, In, Ker, Out, stream);
   }
   if (st == CONV_ENOPLAN && dtype == CONV_DTYPE_BF16) return run_bf16_widened(s, In, Ker, Out, false, stream);
   if (st != CONV_OK) return st;
@@ -571,15 +581,17 @@ int conv_fwd_bf16_out(int N, int C, int K, int H, int W, int R, int S, const uin
   if (!In || !Ker || !Out) return CONV_ENULL;
   Entry e;
   const Shape sh{N, C, K, H, W, R, S};
-  routed_entry(sh, CONV_DTYPE_BF16, alignment_of(In, Ker), &e);
+  const int align = alignment_of(In, Ker);
+  routed_entry(sh, CONV_DTYPE_BF16, align, &e);
   const bool pair_possible = (W - S + 1) % 8 == 0 && (reinterpret_cast<uintptr_t>(Out) & 15) == 0;
   if (takes_split(e, stream, false)) {
-    Need need;
-    reserve_planned(bf16_out_need(sh, alignment_of(In, Ker), pair_possible, &need), need, stream);
-    return run_split(split_entry(split_shape(N, C, K, H, W, R, S, 1, 1, 0, 0, CONV_DTYPE_BF16)), true, In, Ker, Out,
-                     stream);
+    SplitEntry se = split_entry(split_shape(N, C, K, H, W, R, S, 1, 1, 0, 0, CONV_DTYPE_BF16));
+    Need& need = se.out_need[pair_possible];
+    if (align != ALIGN_ALL) (void)bf16_out_need(sh, align, pair_possible, &(need = Need()));
+    reserve_planned(need, stream);
+    return run_split(se, true, In, Ker, Out, stream);
   }
-  st = cached_entry_bf16_out(sh, alignment_of(In, Ker), pair_possible, &e);
+  st = cached_entry_bf16_out(sh, align, pair_possible, &e);
   if (st == CONV_ENOPLAN) return run_bf16_widened(sh, In, Ker, Out, true, stream);
   if (st != CONV_OK) return st;
   return launch_bf16_out(*e.v, e.g, In, Ker, Out, stream);
@@ -696,10 +708,11 @@ int conv_fwd_ex(int N, int C, int K, int H, int W, int R, int S, int stride_h, i
   const int rt = ex_route(p, dtype, In, Ker, stream, false, &split, &x);
   if (rt != CONV_OK) return rt;
   if (split) {
-    Need need;
-    reserve_planned(ex_need(p, dtype, In, Ker, &need), need, stream);
-    return run_split(split_entry(split_shape(N, C, K, H, W, R, S, stride_h, stride_w, pad_h, pad_w, dtype)), false, In,
-                     Ker, Out, stream);
+    SplitEntry se = split_entry(split_shape(N, C, K, H, W, R, S, stride_h, stride_w, pad_h, pad_w, dtype));
+    const int align = alignment_of(In, Ker);
+    if (align != ALIGN_ALL) (void)ex_need(p, dtype, align, &(se.need = Need()));
+    reserve_planned(se.need, stream);
+    return run_split(se, false, In, Ker, Out, stream);
   }
   return run_ex(p, dtype, In, Ker, Out, stream, x);
 }
@@ -712,7 +725,7 @@ int conv_fwd_ex_noalloc(int N, int C, int K, int H, int W, int R, int S, int str
   if (!In || !Ker || !Out) return CONV_ENULL;
   if (dtype != CONV_DTYPE_F32 && dtype != CONV_DTYPE_BF16) return CONV_EINVAL;
   Need planned;
-  st = ex_need(p, dtype, In, Ker, &planned);
+  st = ex_need(p, dtype, alignment_of(In, Ker), &planned);
   if (st != CONV_OK) return st;
   size_t need = planned.total;
   if (need > (size_t)CONV_NOALLOC_SCRATCH_BYTES) return CONV_ESCRATCH;

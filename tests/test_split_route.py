@@ -266,6 +266,25 @@ def test_route_needs_a_plan():
     assert B.conv_fwd_split_plan(*dims, 1, 3) is None
 
 
+def test_a_missing_plan_is_remembered():
+    """bf16 layers without a bf16 plan (5x5 taps) look that up on every call:
+    it must not search the plans again each time (17 us)."""
+    import ctypes
+    import time
+
+    L, plan = B.lib(), B.ConvPlan()
+
+    def best(dims, status):
+        t = []
+        for _ in range(200):
+            a = time.perf_counter()
+            st = L.conv_fwd_plan(*dims, B.CONV_DTYPE_BF16, ctypes.byref(plan))
+            t.append(time.perf_counter() - a)
+            assert st == status
+        return min(t)
+    assert best((2, 24, 40, 14, 12, 5, 5), B.CONV_ENOPLAN) <= 4 * best((2, 24, 40, 14, 12, 3, 3), B.CONV_OK)
+
+
 @pytest.mark.parametrize("dims", [(298261, 1, 2, 60, 60, 5, 5), (65535, 1, 2, 128, 128, 5, 5),
                                   (1369568, 1, 2, 28, 28, 5, 5)], ids=str)
 def test_grid_fits_a_launch(dims):
