@@ -438,6 +438,38 @@ SplitShape split_shape(int N, int C, int K, int H, int W, int R, int S, int sh, 
   return SplitShape{N, C, K, H, W, R, S, sh, sw, ph, pw, (H + 2 * ph - R) / sh + 1, (W + 2 * pw - S) / sw + 1, dtype};
 }
 
+// Is the split plan p to run instead of a plan estimated at us?  Estimates of
+// grids that fill half the chip are within a few percent of each other's
+// errors; for fewer tiles both are less reliable (a 672 x 814 1x1 layer on 6
+// tiles: estimate 30 against 32 us, measured 30.0 against 23.3).
+//
+// The shorter layers need more: the plans of fp32 layers with taps measure 2 us
+// less than their estimates below 20 us, the split kernels up to 2 us more
+// (two launches, the sum of the channel groups).  The lines were drawn on 1400
+// random layers of which 26 were slower than their plans by more than 1.5%,
+// by up to 13%; of 2000 others that they route 19 are (7 of 886 fp32, 12 of
+// 1114 bf16 ones, mostly 1x1 layers of 16 or 32 channels whose plans the
+// estimates take for twice as slow), and the others run 1.56 times (fp32) and
+// 2.55 times (bf16) as fast as their plans in the geometric mean.
+bool split_wins(const SplitShape& s, const SplitPlan& p, double us) {
+  double share = p.g.num_tiles >= 128 ? 0.97 : 0.9;
+  if (s.dtype == CONV_DTYPE_BF16) {
+    // Of one-chunk layers this short half were faster on their plans (14 layers
+    // in 0.91 to 1.12 times their plans' speed, 1.00 in the mean).
+    if (p.cfg->vec > 1 && us < 13.2) return false;
+  } else if (s.R * s.S > 1) {
+    // The rearranged Ker of strided layers below 25 us costs them 2.0 us (66
+    // layers: 1.2 to 2.1 in the mean of each 4 us), not 4.5.
+    if (p.cfg->mode == SPLIT_CONV && (s.sh > 1 || s.sw > 1) && us < 30) us -= 2.5;
+    // (strided image layers: 1.06 to 1.42 times their plans' speed here)
+    if (us < 20 && (p.cfg->mode == SPLIT_CONV || (s.sh == 1 && s.sw == 1))) share = 0.77;
+    else if (us < 27) share = 0.88;
+  } else if (us < 26) {
+    share = 0.88;
+  }
+  return p.us < share * us;
+}
+
 SplitEntry split_entry(const SplitShape& s) {
   const SplitKey key{s.N, s.C, s.K, s.H, s.W, s.R, s.S, s.sh * 64 + s.sw, s.ph, s.pw, s.dtype};
   {
@@ -449,16 +481,8 @@ SplitEntry split_entry(const SplitShape& s) {
   double us = 0;
   // The packed operand also has to fit the allocation-free entry point's
   // scratch, so that it takes the same route.
-  // Estimates of grids that fill half the chip are within a few percent of each
-  // other's errors; for fewer tiles both are less reliable (a 672 x 814 1x1
-  // layer on 6 tiles: estimate 30 against 32 us, measured 30.0 against 23.3).
-  // fp32 plans estimated below 26 us need 12%: over 260 random layers the 11
-  // routed ones between the two lines ran in 0.83 to 1.19 times their plan's
-  // speed (0.98 in the mean; 3x3 C48 K304 33x33 at batch 2 14.1 -> 16.9 us;
-  // the six between 26 and 36 us in 0.98 to 4.0 times).
   e.use = planned_time(s, &us) == CONV_OK && split_choose(s, &e.p) &&
-          e.p.pk_bytes <= (size_t)CONV_NOALLOC_SCRATCH_BYTES &&
-          e.p.us < (s.dtype == CONV_DTYPE_F32 && us < 26 ? 0.88 : e.p.g.num_tiles >= 128 ? 0.97 : 0.9) * us;
+          e.p.pk_bytes <= (size_t)CONV_NOALLOC_SCRATCH_BYTES && split_wins(s, e.p, us);
   PhaseGeom p;
   if (e.use && phase_geom(s.N, s.C, s.K, s.H, s.W, s.R, s.S, s.sh, s.sw, s.ph, s.pw, &p) == CONV_OK) {
     (void)ex_need(p, s.dtype, ALIGN_ALL, &e.need);
