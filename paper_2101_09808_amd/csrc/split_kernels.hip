@@ -127,18 +127,16 @@ __device__ __forceinline__ void put_fragment(const T (&x)[8], v4u* dst) {
 //   CONV, POINT: channel octet u % co of the chunk at tap u / co (POINT: rows
 //   are pixels of In, one tap); IMAGE: columns s = 2 (u % Sp), + 1 of kernel
 //   row u / Sp, 4 channels each.
-template <int MODE, int NPL>
+template <int MODE>
 __global__ void __launch_bounds__(256)
-split_pack_kernel(const void* __restrict__ SrcV, v4u* __restrict__ Pk, const SplitGeom g) {
-  typedef typename std::conditional<NPL == 3, float, unsigned short>::type T;
-  const T* Src = static_cast<const T*>(SrcV);
+split_pack_kernel(const float* __restrict__ Src, v4u* __restrict__ Pk, const SplitGeom g) {
   const int F = g.nchunks * g.steps;
   const int lane = threadIdx.x & 63;
   const int w = blockIdx.x * 4 + (threadIdx.x >> 6);  // (block, chunk, step)
   if (w >= g.blocks * F) return;
   const int blk = w / F, f = w - blk * F, ch = f / g.steps, m = f - ch * g.steps;
   const int u = 4 * m + (lane >> 4), row = blk * 16 + (lane & 15);
-  T x[8];
+  float x[8];
   if constexpr (MODE == SPLIT_IMAGE) {
     const int Sp = (g.S + 1) / 2, r = u / Sp, s0 = 2 * (u - r * Sp);
     const bool ok = row < g.K && r < g.R;
@@ -146,8 +144,8 @@ split_pack_kernel(const void* __restrict__ SrcV, v4u* __restrict__ Pk, const Spl
     for (int e = 0; e < 8; ++e) {
       const int c = e & 3, s = s0 + (e >> 2);
       const bool v = ok && c < g.C && s < g.S;
-      const T t = Src[v ? (((size_t)row * g.C + c) * g.R + r) * g.S + s : 0];
-      x[e] = v ? t : T(0);
+      const float t = Src[v ? (((size_t)row * g.C + c) * g.R + r) * g.S + s : 0];
+      x[e] = v ? t : 0.f;
     }
   } else {
     const int c0 = ch * g.co * 8 + u * 8, PQ = g.P * g.Q;
@@ -156,11 +154,11 @@ split_pack_kernel(const void* __restrict__ SrcV, v4u* __restrict__ Pk, const Spl
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int c = c0 + e;
-      const T t = Src[((size_t)n * g.C + min(c, g.C - 1)) * PQ + p];
-      x[e] = ok && c < g.C ? t : T(0);
+      const float t = Src[((size_t)n * g.C + min(c, g.C - 1)) * PQ + p];
+      x[e] = ok && c < g.C ? t : 0.f;
     }
   }
-  put_fragment<NPL>(x, Pk + (size_t)w * NPL * 64 + lane);
+  put_fragment<3>(x, Pk + (size_t)w * 3 * 64 + lane);
 }
 
 // CONV: one wave packs one channel octet of a 16-row block: its 16 runs of
@@ -238,6 +236,8 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
   constexpr int BK = 16 * WK * NWK;  // packed rows per workgroup (POINT: pixels)
   constexpr int BP = 16 * WP * NWP;  // staged rows per workgroup (POINT: output channels)
   constexpr int ISZ = NPL == 3 ? 4 : 2;
+  static_assert(VEC == 1 || (MODE == SPLIT_CONV && NPL == 1 && ONE), "vector staging: one chunk of bf16");
+  static_assert(MODE == SPLIT_CONV || NPL == 3, "bf16 layers are staged by octets");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wk = wave % NWK, wp = (wave / NWK) % NWP, wc = wave / (NWK * NWP);
@@ -304,10 +304,10 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
     // not gain: 3x3 C128 46.3 -> 49.8 us, C512 60.4 -> 60.6 us.)
     // Four neighbouring input pixels per item, inside the image row: the last
     // group of a row starts early enough to end in it (pixels staged twice
-    // get the same bytes).  Columns in the padding are zeroed here, in both
-    // buffers; no item writes them.
+    // get the same bytes).  Columns in the padding are zeroed here; no item
+    // writes them.
     const int x0 = q0 * g.sw - g.pw;  // input column of the tile's first staged one
-    const int xa = max(x0, 0) & (NPL == 3 ? ~0 : ~1);  // bf16: dword-aligned groups
+    const int xa = max(x0, 0) & ~1;  // dword-aligned groups
     if (g.pw > 0) {
       for (int u = tid; u < g.co * g.E; u += NT) {
         const int o = fdiv(u, g.dv_Ez), e = u - o * g.E;
@@ -315,9 +315,7 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
         const int f = fdiv(prow, g.dv_rows);
         const int xx = x0 + x * g.sw + f - fdiv(f, g.dv_nb) * g.nb;
         if ((unsigned)xx < (unsigned)g.W) continue;
-        for (int p = 0; p < NPL; ++p)
-          for (int bf = 0; bf < (ONE ? 1 : 2); ++bf)
-            *reinterpret_cast<v4u*>(smem + bf * g.buf_bytes + (p * g.co + o) * g.Epad * 16 + e * 16) = v4u{0, 0, 0, 0};
+        *reinterpret_cast<v4u*>(smem + (o * g.Epad + e) * 16) = v4u{0, 0, 0, 0};
       }
     }
     int it = tid < g.items ? tid : tid % g.items;
@@ -373,9 +371,8 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
   const auto irsrc = make_rsrc(MODE == SPLIT_POINT ? KerV : InV, g.st_bytes);
   const auto prsrc = make_rsrc(Pk, g.pk_bytes);
 
-  typedef unsigned stg_t __attribute__((ext_vector_type(VEC == 1 ? 2 : NPL == 3 ? 4 : 2)));
   unsigned stg[VEC > 1 ? 1 : NI][8];
-  stg_t stv[VEC > 1 ? NI : 1][8];
+  v2u stv[VEC > 1 ? NI : 1][8];
   // Load e of item i of chunk ch (scalar offsets stay inside the tensor, so
   // that the range check's difference is positive).
   constexpr int LPI = MODE == SPLIT_POINT ? 2 : 8;  // loads per item
@@ -391,10 +388,7 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
       const int c = ch * g.co * 8 + e;
       const unsigned off = c + 8 * (int)loff[i] >= g.C ? kOob : goff[i];
       const int so = min(c, g.C - 1) * HW * ISZ;
-      if constexpr (NPL == 3)
-        stv[i][e] = __builtin_bit_cast(stg_t, __builtin_amdgcn_raw_buffer_load_b128(irsrc, off, so, 0));
-      else
-        stv[i][e] = __builtin_bit_cast(stg_t, __builtin_amdgcn_raw_buffer_load_b64(irsrc, off, so, 0));
+      stv[i][e] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(irsrc, off, so, 0));
     } else {
       unsigned off;
       int so;
@@ -418,9 +412,8 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
   auto convert_piece = [&](int i, int q, unsigned char* buf) {
     const int e = q & 3, px = q >> 2, ci = VEC > 1 ? 0 : i;
     if constexpr (NPL == 3) {
-      unsigned lo, hi, a, b, c;
-      if constexpr (VEC > 1) lo = stv[i][2 * e][px], hi = stv[i][2 * e + 1][px];
-      else lo = stg[i][2 * e], hi = stg[i][2 * e + 1];
+      const unsigned lo = stg[i][2 * e], hi = stg[i][2 * e + 1];
+      unsigned a, b, c;
       split2(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi), a, b, c);
       cvt[ci][0][e] = a; cvt[ci][1][e] = b; cvt[ci][2][e] = c;
     } else if constexpr (VEC > 1) {
@@ -906,11 +899,9 @@ int split_launch(const SplitPlan& p, bool out_bf16, const void* In, const void* 
   } else {
     const dim3 grid((g.blocks * g.nchunks * g.steps + 3) / 4);
     if (p.cfg->mode == SPLIT_POINT)
-      hipLaunchKernelGGL((split_pack_kernel<SPLIT_POINT, 3>), grid, dim3(256), 0, st, In, pk, g);
-    else if (p.cfg->npl == 3)
-      hipLaunchKernelGGL((split_pack_kernel<SPLIT_IMAGE, 3>), grid, dim3(256), 0, st, Ker, pk, g);
+      hipLaunchKernelGGL(split_pack_kernel<SPLIT_POINT>, grid, dim3(256), 0, st, static_cast<const float*>(In), pk, g);
     else
-      hipLaunchKernelGGL((split_pack_kernel<SPLIT_IMAGE, 1>), grid, dim3(256), 0, st, Ker, pk, g);
+      hipLaunchKernelGGL(split_pack_kernel<SPLIT_IMAGE>, grid, dim3(256), 0, st, static_cast<const float*>(Ker), pk, g);
   }
   if (out_bf16)
     hipLaunchKernelGGL(inst->bf16, dim3(g.num_tiles), dim3(p.cfg->threads()), p.lds_bytes, st, In, pk, Ker,

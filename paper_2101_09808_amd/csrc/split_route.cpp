@@ -82,10 +82,10 @@ bool split_geometry(const SplitShape& s, const SplitConfig& c, int tr, int tw, i
     g.E = (int)E;
     g.Epad = (int)cdiv(E + (c.vec > 1 ? 1 : 0), 16) * 16;  // (vector staging: a slot for pixels outside the tile)
     if (c.vec > 1) {
-      // groups of four pixels inside the image row; both column phases of a
-      // stride of 2; bf16 groups are dword-aligned
-      if (s.W < 4 || s.sw > 2 || g.nb != s.sw || (bf16 && s.W % 2)) return false;
-      g.ng = (int)cdiv(std::min<int64_t>(s.W, (int64_t)(tw - 1) * s.sw + s.S + (bf16 ? 1 : 0)), 4);
+      // (bf16) groups of four pixels inside the image row, dword-aligned; both
+      // column phases of a stride of 2
+      if (s.W < 4 || s.sw > 2 || g.nb != s.sw || s.W % 2) return false;
+      g.ng = (int)cdiv(std::min<int64_t>(s.W, (int64_t)(tw - 1) * s.sw + s.S + 1), 4);
       g.E4 = g.na * in_rows * g.ng;
     }
     blocks = kt * (BK / 16);
