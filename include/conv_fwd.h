@@ -420,7 +420,7 @@ int conv_fwd_ex_plan(int N, int C, int K, int H, int W, int R, int S, int stride
  * beyond 2^80, infinities and NaNs leave the split operands' range: a tile
  * (workgroup) with an output that comes out infinite or NaN is computed again
  * for these on the fp32 MFMAs, so they are what fp32 arithmetic gives; an fp32
- * call whose every tile does so takes up to 3.5 times as long (bf16 calls: as
+ * call whose every tile does so takes up to four times as long (bf16 calls: as
  * long as ever).
  * Writes min(cap, CONV_SPLIT_FIELDS) values: 1 if the split-operand kernels
  * run (else all zero), instance id, mode (0 In staged in LDS, 1 the same for

@@ -50,7 +50,7 @@ struct SplitGeom {
 // One compiled instance of the split kernel.
 struct SplitConfig {
   int id, mode;
-  int vec;      // pixels per staging load (CONV: 1 or 4)
+  int vec;      // pixels per staging load (4: bf16 CONV layers of one chunk)
   int wk, wp, nwk, nwp, nwc, npl;
   int ni;       // staging items per thread, at most
   int ns;       // MFMA steps per chunk and wave group

@@ -660,14 +660,16 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
   // The tile again, for its outputs that are not finite, as IEEE arithmetic
   // treats infinities, NaNs and sums beyond the scaled range.  fp32: the
   // operands themselves on the fp32 MFMA (In is staged with the 8 channels of
-  // a slot as floats in the first two planes), summed per chunk and then over
-  // the chunks.  bf16 operands are multiplied as they are, so only the units
-  // past the last tap can spoil an infinity (it meets a zero there).  These
-  // units are masked in both.  Nothing is pipelined: fp32 tiles take two to
-  // three times their first pass (all of In NaN, 3x3 C128 N32: 49 -> 161 us,
-  // 1x1 C1024 K28269: 112 -> 359 us; each lane summing its outputs by itself,
-  // 3.8 and 37 ms; the tile plans 82 and 284 us).  2-norm error on outputs of
-  // 2^100: 3.1e-7 on C128 and 2.3e-7 on C512 (tile plans 6.1e-7 and 4.3e-7).
+  // a slot as floats in the first two planes), each step's 32 products summed
+  // by themselves first: in one chain per chunk the error on six of 19 layers,
+  // one per instance, was above the tile plans' (up to 2.2e-7 against 1.3e-7).
+  // bf16 operands are multiplied as they are, so only the units past the last
+  // tap can spoil an infinity (it meets a zero there).  These units are masked
+  // in both.  Nothing is pipelined: fp32 tiles take two to three times their
+  // first pass (all of In NaN, 3x3 C128 N32: 48 -> 172 us, 1x1 C1024 K28269:
+  // 112 -> 371 us; each lane summing its outputs by itself, 3.8 and 37 ms; the
+  // tile plans 82 and 284 us).  2-norm error on outputs of 2^100: 1.5e-7 on
+  // C128 and 1.6e-7 on C512 (tile plans 6.1e-7 and 4.3e-7).
   unsigned bad[(WK * WP * 4 + 31) / 32] = {};
 #pragma unroll
   for (int b = 0; b < WK * WP * 4; ++b)
@@ -682,7 +684,6 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
   asm volatile("" : "+v"(again), "+v"(thread), "+s"(first));
   row_offsets(again);
   if constexpr (ONE) __builtin_amdgcn_sched_barrier(0);
-  constexpr bool CHAIN = ONE || NPL == 1;  // (bf16: one chain of sums, as in the first pass)
   static_assert(!(ONE && NPL == 1) || NWC == 1, "the sums of the groups overwrite the chunk");
   constexpr bool SERIAL = ONE || NPL == 1;  // an item at a time: fewer registers
   const auto orsrc = make_rsrc(MODE == SPLIT_POINT ? InV : KerV,
@@ -720,12 +721,6 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
       }
       __syncthreads();
     }
-    v4f total[CHAIN ? 1 : WK][CHAIN ? 1 : WP];  // of the chunks before
-    if constexpr (!CHAIN)
-#pragma unroll
-      for (int i = 0; i < WK; ++i)
-#pragma unroll
-        for (int j = 0; j < WP; ++j) total[i][j] = acc[i][j], acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma clang loop unroll(disable)
     for (int m = wc; m < g.steps; m += NWC) {
       const int u = 4 * m + gq, off = tab[u];
@@ -784,11 +779,14 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
             }
           }
 #pragma unroll
-          for (int e = 0; e < 8; ++e)
+          for (int i = 0; i < WK; ++i) {
+            v4f t = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int i = 0; i < WK; ++i)
-              acc[i][j] = MODE == SPLIT_POINT ? __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[i][e], acc[i][j], 0, 0, 0)
-                                              : __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[e], acc[i][j], 0, 0, 0);
+            for (int e = 0; e < 8; ++e)
+              t = MODE == SPLIT_POINT ? __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[i][e], t, 0, 0, 0)
+                                      : __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[e], t, 0, 0, 0);
+            acc[i][j] += t;
+          }
         }
       } else {
         v4u a[WK][NPL], b[NPL];
@@ -804,11 +802,6 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
         }
       }
     }
-    if constexpr (!CHAIN)
-#pragma unroll
-      for (int i = 0; i < WK; ++i)
-#pragma unroll
-        for (int j = 0; j < WP; ++j) acc[i][j] += total[i][j];
   }
   if constexpr (NWC > 1) {
     __syncthreads();
