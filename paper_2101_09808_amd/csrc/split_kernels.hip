@@ -262,9 +262,11 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
   const int n0 = fdiv(rho0, g.dv_P);
   const int nu0 = n0 * g.Hi + (rho0 - n0 * g.P) * g.rm;  // first staged row
 
-  // step table: LDS byte offset of each step's unit per lane group (units
-  // past the last tap read tap 0: the packed operand is zero there), and the
-  // word that says whether a stored output is not finite
+  // step table: LDS byte offset of each step's unit per lane group, and the
+  // word that says whether a stored output is not finite.  The packed operand
+  // is zero in the units past the last tap; they read tap 0 (fp32: an infinity
+  // there makes the output NaN, and the second pass puts that right) or, bf16,
+  // an octet of zeros that the buffers of such layers have behind the others.
   int* tab = reinterpret_cast<int*>(smem + g.tab_off);
   for (int u = tid; u <= 4 * g.steps; u += NT) {
     if constexpr (MODE == SPLIT_IMAGE) {
@@ -273,12 +275,21 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
     } else {
       const int oct = u % g.co;
       int tap = u / g.co;
-      if (MODE == SPLIT_POINT || tap >= g.R * g.S) tap = 0;
+      const bool past = MODE != SPLIT_POINT && tap >= g.R * g.S;
+      if (MODE == SPLIT_POINT || past) tap = 0;
       const int r = tap / g.S, s = tap - r * g.S;
       const int a = r % g.sh, b = s % g.sw;
-      tab[u] = u == 4 * g.steps ? 0 : 16 * (oct * g.Epad + ((a * g.nb + b) * g.in_rows + r / g.sh) * g.in_wp + s / g.sw);
+      int off = 16 * (oct * g.Epad + ((a * g.nb + b) * g.in_rows + r / g.sh) * g.in_wp + s / g.sw);
+      if (NPL == 1 && past) off = 16 * g.co * g.Epad;
+      tab[u] = u == 4 * g.steps ? 0 : off;
     }
   }
+  if constexpr (NPL == 1)
+    if (4 * g.steps > g.co * g.R * g.S)
+      for (int u = tid; u < g.Epad * (ONE ? 1 : 2); u += NT) {
+        const int bf = u >= g.Epad;
+        *reinterpret_cast<v4u*>(smem + bf * g.buf_bytes + 16 * (g.co * g.Epad + u - bf * g.Epad)) = v4u{0, 0, 0, 0};
+      }
 
   // Staging items of this thread: global byte offset (for IMAGE: of either
   // pixel), LDS byte offset (24 bits) and octet.  Slots past the last item
@@ -429,29 +440,21 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
     }
   };
 
-  // LDS byte offset of this lane's staged row (output pixel) of each block
-  unsigned paddr[WP];
-  auto row_offsets = [&](int j16) {
-#pragma unroll
-    for (int j = 0; j < WP; ++j) {
-      const int p = (wp * WP + j) * 16 + j16;
-      if constexpr (MODE == SPLIT_POINT) {
-        paddr[j] = 16u * (unsigned)p;
-      } else {
-        const int t = fdiv(p, g.dv_tw), col = p - t * g.tw;
-        const int rho = rho0 + t;
-        unsigned ad = 0;
-        if (t < g.tr && rho < rho_end) {
-          const int n = fdiv(rho, g.dv_P);
-          const int row = n * g.Hi + (rho - n * g.P) * g.rm - nu0;
-          ad = MODE == SPLIT_IMAGE ? 16u * (unsigned)(row * g.in_wp) + 8u * (unsigned)(col * g.cm)
-                                   : 16u * (unsigned)(row * g.in_wp + col);
-        }
-        paddr[j] = ad;
-      }
-    }
+  // LDS byte offset of a lane's staged row (output pixel) of block j
+  auto row_offset = [&](int j, int lane16) -> unsigned {
+    const int p = (wp * WP + j) * 16 + lane16;
+    if constexpr (MODE == SPLIT_POINT) return 16u * (unsigned)p;
+    const int t = fdiv(p, g.dv_tw), col = p - t * g.tw;
+    const int rho = rho0 + t;
+    if (t >= g.tr || rho >= rho_end) return 0;
+    const int n = fdiv(rho, g.dv_P);
+    const int row = n * g.Hi + (rho - n * g.P) * g.rm - nu0;
+    return MODE == SPLIT_IMAGE ? 16u * (unsigned)(row * g.in_wp) + 8u * (unsigned)(col * g.cm)
+                               : 16u * (unsigned)(row * g.in_wp + col);
   };
-  row_offsets(j16);
+  unsigned paddr[WP];
+#pragma unroll
+  for (int j = 0; j < WP; ++j) paddr[j] = row_offset(j, j16);
 
   // packed operand: steps wc, wc + NWC, ... of each chunk
   const int F = g.nchunks * g.steps;
@@ -631,8 +634,8 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
       return t < g.tr && rho < rho_end && q < g.Q;
     }
   };
-  int at16 = j16;  // (IMAGE: opaque, or the offsets of the staged rows would keep their parts for this: spills)
-  if constexpr (MODE == SPLIT_IMAGE) asm volatile("" : "+v"(at16));
+  int at16 = j16;  // (opaque, or the parts of the staged rows' offsets would be kept in registers till here)
+  asm volatile("" : "+v"(at16));
   float z = 0.f;  // NaN once a stored output is not finite
 #pragma unroll
   for (int j = 0; j < WP; ++j)
@@ -647,52 +650,49 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
       for (int v = 0; v < 4; ++v) {
         if (k0 + v >= g.K) continue;
         const float x = acc[i][j][v];
-        z = __builtin_fmaf(x, 0.f, z);
+        if constexpr (NPL == 3) z = __builtin_fmaf(x, 0.f, z);
         o[(size_t)v * PQ] = (OT)(NPL == 3 ? x * kUnscale : x);
       }
     }
-  if (NPL == 1 && 4 * g.steps == g.co * g.R * g.S) return;  // no unit past the last tap
-  int* nonfinite = reinterpret_cast<int*>(smem + g.tab_off) + 4 * g.steps;
-  if (z != z) *nonfinite = 1;
-  __syncthreads();
-  if (__builtin_expect(__builtin_amdgcn_readfirstlane(*nonfinite) == 0, 1)) return;
+  if constexpr (NPL == 3) {
+    int* nonfinite = reinterpret_cast<int*>(smem + g.tab_off) + 4 * g.steps;
+    if (z != z) *nonfinite = 1;
+    __syncthreads();
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(*nonfinite) == 0, 1)) return;
 
-  // The tile again, for its outputs that are not finite, as IEEE arithmetic
-  // treats infinities, NaNs and sums beyond the scaled range.  fp32: the
-  // operands themselves on the fp32 MFMA (In is staged with the 8 channels of
-  // a slot as floats in the first two planes), each step's 32 products summed
-  // by themselves first: in one chain per chunk the error on six of 19 layers,
-  // one per instance, was above the tile plans' (up to 2.2e-7 against 1.3e-7).
-  // bf16 operands are multiplied as they are, so only the units past the last
-  // tap can spoil an infinity (it meets a zero there).  These units are masked
-  // in both.  Nothing is pipelined: fp32 tiles take two to three times their
-  // first pass (all of In NaN, 3x3 C128 N32: 48 -> 172 us, 1x1 C1024 K28269:
-  // 112 -> 371 us; each lane summing its outputs by itself, 3.8 and 37 ms; the
-  // tile plans 82 and 284 us).  2-norm error on outputs of 2^100: 1.5e-7 on
-  // C128 and 1.6e-7 on C512 (tile plans 6.1e-7 and 4.3e-7).
-  unsigned bad[(WK * WP * 4 + 31) / 32] = {};
+    // The tile again, for its outputs that are not finite, as IEEE arithmetic
+    // treats infinities, NaNs and sums beyond the scaled range (bf16 operands
+    // are multiplied as they are and need none of this): the operands
+    // themselves on the fp32 MFMA, In staged with the 8 channels of a slot as
+    // floats in the first two planes, the units past the last tap masked, each
+    // step's 32 products summed by themselves first (in one chain per chunk the
+    // error on six of 19 layers, one per instance, was above the tile plans', up
+    // to 2.2e-7 against 1.3e-7).  Nothing is pipelined: a tile takes two to
+    // three times its first pass (all of In NaN, 3x3 C128 N32: 48 -> 172 us, 1x1
+    // C1024 K28269: 112 -> 371 us; each lane summing its outputs by itself, 3.8
+    // and 37 ms; the tile plans 82 and 284 us).  2-norm error on outputs of
+    // 2^100: 1.5e-7 on C128 and 1.6e-7 on C512 (tile plans 6.1e-7 and 4.3e-7).
+    unsigned bad[(WK * WP * 4 + 31) / 32] = {};
 #pragma unroll
-  for (int b = 0; b < WK * WP * 4; ++b)
-    if (!(__builtin_fabsf(acc[(b >> 2) / WP][(b >> 2) % WP][b & 3]) < __builtin_inff())) bad[b / 32] |= 1u << (b % 32);
-  if constexpr (ONE) __builtin_amdgcn_sched_barrier(0);
+    for (int b = 0; b < WK * WP * 4; ++b)
+      if (!(__builtin_fabsf(acc[(b >> 2) / WP][(b >> 2) % WP][b & 3]) < __builtin_inff())) bad[b / 32] |= 1u << (b % 32);
+    if constexpr (ONE) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int i = 0; i < WK; ++i)
+    for (int i = 0; i < WK; ++i)
 #pragma unroll
-    for (int j = 0; j < WP; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-  // (opaque indices, or parts of the first pass's offsets would be kept in registers for this one)
-  int again = j16, thread = tid, first = 0;
-  asm volatile("" : "+v"(again), "+v"(thread), "+s"(first));
-  row_offsets(again);
-  if constexpr (ONE) __builtin_amdgcn_sched_barrier(0);
-  static_assert(!(ONE && NPL == 1) || NWC == 1, "the sums of the groups overwrite the chunk");
-  constexpr bool SERIAL = ONE || NPL == 1;  // an item at a time: fewer registers
-  const auto orsrc = make_rsrc(MODE == SPLIT_POINT ? InV : KerV,
-                               4u * (unsigned)(MODE == SPLIT_POINT ? g.N * g.C * PQ : g.K * g.C * g.R * g.S));
+      for (int j = 0; j < WP; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    // (opaque indices, or parts of the first pass's offsets would be kept in registers for this one)
+    int again = j16, thread = tid, first = 0;
+    asm volatile("" : "+v"(again), "+v"(thread), "+s"(first));
+#pragma unroll
+    for (int j = 0; j < WP; ++j) paddr[j] = row_offset(j, again);
+    if constexpr (ONE) __builtin_amdgcn_sched_barrier(0);
+    const auto orsrc = make_rsrc(MODE == SPLIT_POINT ? InV : KerV,
+                                 4u * (unsigned)(MODE == SPLIT_POINT ? g.N * g.C * PQ : g.K * g.C * g.R * g.S));
 #pragma clang loop unroll(disable)
-  for (int ch = first; ch < (ONE ? 1 : g.nchunks); ++ch) {
-    if constexpr (!ONE || NPL == 3) {  // (else the chunk is still in place)
+    for (int ch = first; ch < (ONE ? 1 : g.nchunks); ++ch) {
       __syncthreads();  // (buffer 0 was read)
-      if constexpr (!SERIAL)
+      if constexpr (!ONE)
 #pragma unroll
         for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -700,7 +700,7 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
       [[maybe_unused]] int it = thread < g.items ? thread : thread % g.items;
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
-        if constexpr (SERIAL) {
+        if constexpr (ONE) {  // (an item at a time: fewer registers)
           __builtin_amdgcn_sched_barrier(0);
           if constexpr (MODE == SPLIT_IMAGE) {
             if (i > 0 && it + NT < g.items) it += NT;
@@ -709,26 +709,19 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
 #pragma unroll
           for (int e = 0; e < LPI; ++e) load_in(i, e, ch);
         }
-        if constexpr (NPL == 3) {
-          constexpr int M1 = MODE == SPLIT_IMAGE ? 4 : 2, M2 = MODE == SPLIT_IMAGE ? 2 : 4;  // IMAGE: 2 pixels x 2 channels
-          unsigned char* d = smem + (loff[i] & 0xffffffu);
-          *reinterpret_cast<v4u*>(d) = v4u{stg[i][0], stg[i][1], stg[i][M1], stg[i][M1 + 1]};
-          *reinterpret_cast<v4u*>(d + pl_bytes) = v4u{stg[i][M2], stg[i][M2 + 1], stg[i][6], stg[i][7]};
-        } else {
-#pragma unroll
-          for (int q = 0; q < PPI; ++q) convert_piece(i, q, smem);
-        }
+        constexpr int M1 = MODE == SPLIT_IMAGE ? 4 : 2, M2 = MODE == SPLIT_IMAGE ? 2 : 4;  // IMAGE: 2 pixels x 2 channels
+        unsigned char* d = smem + (loff[i] & 0xffffffu);
+        *reinterpret_cast<v4u*>(d) = v4u{stg[i][0], stg[i][1], stg[i][M1], stg[i][M1 + 1]};
+        *reinterpret_cast<v4u*>(d + pl_bytes) = v4u{stg[i][M2], stg[i][M2 + 1], stg[i][6], stg[i][7]};
       }
       __syncthreads();
-    }
 #pragma clang loop unroll(disable)
-    for (int m = wc; m < g.steps; m += NWC) {
-      const int u = 4 * m + gq, off = tab[u];
-      const int Sp = (g.S + 1) / 2;
-      const int tap = MODE == SPLIT_IMAGE ? u / Sp : u / g.co;  // IMAGE: kernel row
-      const int oct = MODE == SPLIT_IMAGE ? 2 * (u - tap * Sp) : u - tap * g.co;  // IMAGE: first column
-      const bool real = tap < (MODE == SPLIT_IMAGE ? g.R : g.R * g.S);
-      if constexpr (NPL == 3) {
+      for (int m = wc; m < g.steps; m += NWC) {
+        const int u = 4 * m + gq, off = tab[u];
+        const int Sp = (g.S + 1) / 2;
+        const int tap = MODE == SPLIT_IMAGE ? u / Sp : u / g.co;  // IMAGE: kernel row
+        const int oct = MODE == SPLIT_IMAGE ? 2 * (u - tap * Sp) : u - tap * g.co;  // IMAGE: first column
+        const bool real = tap < (MODE == SPLIT_IMAGE ? g.R : g.R * g.S);
         float a[WK][8];
 #pragma unroll
         for (int i = 0; i < WK; ++i) {
@@ -788,41 +781,29 @@ split_conv_kernel(const void* __restrict__ InV, const v4u* __restrict__ Pk, cons
             acc[i][j] += t;
           }
         }
-      } else {
-        v4u a[WK][NPL], b[NPL];
+      }
+    }
+    if constexpr (NWC > 1) {
+      __syncthreads();
+      sum_groups();
+    }
+    asm volatile("" : "+v"(again));
 #pragma unroll
-        for (int i = 0; i < WK; ++i) load_a(a, i, ch, m);
+    for (int j = 0; j < WP; ++j)
 #pragma unroll
-        for (int j = 0; j < WP; ++j) {
-          load_b(b, smem, paddr[j] + off);
+      for (int i = 0; i < WK; ++i) {
+        int n, h, q, k0;
+        const bool ok = locate(again, i, j, n, h, q, k0);
+        if (NWC > 1 && (i * WP + j) % NWC != wc) continue;
+        if (!ok) continue;
+        OT* o = Out + ((size_t)n * g.K + k0) * PQ + h * g.Q + q;
 #pragma unroll
-          for (int x = 0; x < 4; ++x) b[0][x] = real ? b[0][x] : 0u;
-#pragma unroll
-          for (int i = 0; i < WK; ++i) mma1(a[i][0], b[0], acc[i][j]);
+        for (int v = 0; v < 4; ++v) {
+          const int b = (i * WP + j) * 4 + v;
+          if (k0 + v < g.K && (bad[b / 32] >> (b % 32) & 1)) o[(size_t)v * PQ] = (OT)acc[i][j][v];
         }
       }
-    }
   }
-  if constexpr (NWC > 1) {
-    __syncthreads();
-    sum_groups();
-  }
-  asm volatile("" : "+v"(again));
-#pragma unroll
-  for (int j = 0; j < WP; ++j)
-#pragma unroll
-    for (int i = 0; i < WK; ++i) {
-      int n, h, q, k0;
-      const bool ok = locate(again, i, j, n, h, q, k0);
-      if (NWC > 1 && (i * WP + j) % NWC != wc) continue;
-      if (!ok) continue;
-      OT* o = Out + ((size_t)n * g.K + k0) * PQ + h * g.Q + q;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int b = (i * WP + j) * 4 + v;
-        if (k0 + v < g.K && (bad[b / 32] >> (b % 32) & 1)) o[(size_t)v * PQ] = (OT)acc[i][j][v];
-      }
-    }
 }
 
 typedef void (*SplitFnF)(const void*, const v4u*, const void*, float*, SplitGeom);

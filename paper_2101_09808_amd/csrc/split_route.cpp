@@ -103,7 +103,8 @@ bool split_geometry(const SplitShape& s, const SplitConfig& c, int tr, int tw, i
   if (pk >= lim || blocks >= (1 << 24)) return false;
   g.blocks = (int)blocks;
   g.pk_bytes = (unsigned)pk;
-  g.buf_bytes = c.npl * co * g.Epad * 16;
+  // (bf16: units past the last tap read an octet of zeros)
+  g.buf_bytes = (c.npl * co + (bf16 && 4 * steps > (int64_t)co * s.R * s.S ? 1 : 0)) * g.Epad * 16;
   const int stage = (c.one ? 1 : 2) * g.buf_bytes;
   const int red = c.nwc > 1 ? NT / 64 * c.wk * c.wp * 1024 : 0;
   g.tab_off = std::max(stage, red);

@@ -104,7 +104,11 @@ def emulate(s, g, In, Ker, wgs):
         prow = np.arange(BK) + (rt if point else kt) * BK
         acc = np.zeros((BK, BP))
         for ch in range(g["nchunks"]):
-            lds = np.full((g["co"] * g["Epad"], 8), np.nan)
+            lds = np.full(((g["co"] + 1) * g["Epad"], 8), np.nan)
+            zeros = g["npl"] == 1 and 4 * g["steps"] > g["co"] * R * S  # an octet for the units past the last tap
+            if zeros:
+                lds[g["co"] * g["Epad"]:] = 0
+                assert g["buf_bytes"] == 16 * len(lds)
             if g["vec"] > 1:
                 stage_vec(s, g, In, lds, ch, nu0, q0)
             for it in range(g["items"] if g["vec"] == 1 else 0):
@@ -154,6 +158,8 @@ def emulate(s, g, In, Ker, wgs):
                         r, ss = t // S, t % S
                         off = 8 * (o * g["Epad"] + ((r % st * g["nb"] + ss % st) * g["in_rows"] + r // st) * g["in_wp"]
                                    + ss // st)
+                        if zeros and not real:
+                            off = 8 * g["co"] * g["Epad"]
                         c0 = (ch * g["co"] + o) * 8
                         for i, k in enumerate(prow):
                             n = max(0, min(8, C - c0))
@@ -211,6 +217,10 @@ EMULATED = [
     # four pixels per load: K <= 32 and more, padded, a tail of columns
     ConvShape("sp_bf16_vec_k32", 9, 32, 32, 60, 50, 3, 3, "bf16", 706),
     ConvShape("sp_bf16_vec_k32_pad", 5, 30, 24, 70, 62, 3, 3, "bf16", 707, 1, 1),
+    # units past the last tap: 18 of 20, 50 of 52, 35 of 36
+    ConvShape("sp_bf16_s2_c3", 1, 3, 7, 56, 61, 3, 3, "bf16", 708, 2, 0),
+    ConvShape("sp_bf16_5x5_c17", 1, 17, 7, 7, 6, 5, 5, "bf16", 709),
+    ConvShape("sp_bf16_7x5", 8, 8, 200, 43, 63, 7, 5, "bf16", 710, 3, 1),
 ]
 
 
