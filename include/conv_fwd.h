@@ -309,7 +309,8 @@ int conv_fwd_candidates(int N, int C, int K, int H, int W, int R, int S, int dty
  * and tensor alignment: later
  * conv_fwd / conv_fwd_bf16 / conv_fwd_plan calls for them return or run it,
  * unless the layer is on the split-operand route (conv_fwd_split_plan) and
- * that, timed the same way, was faster still: then the compute calls stay on it.
+ * that, timed the same way (with fp32 Out), was faster still: then the compute
+ * calls stay on it.  A layer that is not on the route is not tried on it.
  *   dtype      : CONV_DTYPE_*; In and Ker as for conv_fwd or conv_fwd_bf16
  *   Out        : overwritten with Eq. (1) (every candidate computes it)
  *   top_n      : 1 .. CONV_TUNE_MAX;  reps : 1 .. 1000
@@ -411,17 +412,19 @@ int conv_fwd_ex_plan(int N, int C, int K, int H, int W, int R, int S, int stride
  * products the six that matter at fp32 precision are summed in fp32 (measured
  * closer to the 64-bit result than the fp32 MFMA kernels); bf16 operands are
  * taken as they are.  The compute calls take them where their estimated time
- * is below the plan's (by 3% or more): most bf16 layers, fp32 layers of more than
- * about half a GFLOP.  They pack Ker (for 1x1 layers with many output
- * channels: In) into a per-stream workspace on every call, so under graph
- * capture conv_fwd, conv_fwd_bf16, conv_fwd_bf16_out and conv_fwd_ex run the
- * plan; conv_fwd_ex_noalloc packs into its static scratch and takes the same
- * route with and without capture.  fp32 sums
- * beyond 2^80, infinities and NaNs leave the split operands' range: a tile
- * (workgroup) with an output that comes out infinite or NaN is computed again
- * for these on the fp32 MFMAs, so they are what fp32 arithmetic gives; an fp32
- * call whose every tile does so takes up to four times as long (bf16 calls: as
- * long as ever).
+ * is below the plan's by 3% or more, short layers by 10% to 23%: most bf16
+ * layers, most larger fp32 layers with taps, strided image layers.  They pack Ker (for
+ * 1x1 layers with many output channels: In) into a per-stream workspace on
+ * every call, so under graph capture conv_fwd, conv_fwd_bf16,
+ * conv_fwd_bf16_out and conv_fwd_ex run the plan, at the plan's speed and with
+ * the plan's bits (within rounding of the eager call's); so that this needs no
+ * allocation, eager calls keep the plan's workspaces too.  conv_fwd_ex_noalloc
+ * packs into its static scratch and takes the same route with and without
+ * capture.  fp32 sums beyond 2^80, infinities and NaNs leave the split
+ * operands' range: a tile (workgroup) with an output that comes out infinite
+ * or NaN is computed again for these on the fp32 MFMAs, so they are what fp32
+ * arithmetic gives; an fp32 call whose every tile does so takes up to four
+ * times as long (bf16 calls: as long as ever).
  * Writes min(cap, CONV_SPLIT_FIELDS) values: 1 if the split-operand kernels
  * run (else all zero), instance id, mode (0 In staged in LDS, 1 the same for
  * at most 4 channels, 2 Ker staged), pixels per staging load, 16-row blocks per wave of the packed and

@@ -406,7 +406,11 @@ int planned_time(const SplitShape& s, double* us) {
     }
     // (the transposing bf16 kernel's ranking times were taken between events:
     // 73 us for the 226x226 layer that runs in 59-70 us, 16.0 us for a
-    // 166x106 one that runs in 12.3 us)
+    // 166x106 one that runs in 12.3 us.  Of 61 wide layers of up to 32 channels
+    // 8 keep their plans with this: five ran faster there, by 4% to 27%, and
+    // three, 163x172 at batch 2, 163x144 at batch 8 and 128x96 at batch 4, would
+    // have been 1.4 to 1.7 times as fast on the split kernels.  bf16 Out of the
+    // 226x226 layer too: 63.9 against 56.9 us, with fp32 Out 59.6 against 65.9.)
     if (st == CONV_OK) *t = e.plan.rank_us * (e.v->family == FAMILY_BF16_TR ? 0.7 : 1.0) + extra;
     return st;
   };
@@ -447,10 +451,10 @@ SplitShape split_shape(int N, int C, int K, int H, int W, int R, int S, int sh, 
 // less than their estimates below 20 us, the split kernels up to 2 us more
 // (two launches, the sum of the channel groups).  The lines were drawn on 1400
 // random layers of which 26 were slower than their plans by more than 1.5%,
-// by up to 13%; of 2000 others that they route 19 are (7 of 886 fp32, 12 of
-// 1114 bf16 ones, mostly 1x1 layers of 16 or 32 channels whose plans the
-// estimates take for twice as slow), and the others run 1.56 times (fp32) and
-// 2.55 times (bf16) as fast as their plans in the geometric mean.
+// by up to 13%; of 2000 others that they route 16 are (8 of 886 fp32, 8 of 1114
+// bf16; worst 3x3 stride 2 C19 K16 91x91 at batch 9, 18.8 -> 21.5 us), and all
+// run 1.55 times (fp32) and 2.56 times (bf16) as fast as their plans in the
+// geometric mean.
 bool split_wins(const SplitShape& s, const SplitPlan& p, double us) {
   double share = p.g.num_tiles >= 128 ? 0.97 : 0.9;
   if (s.dtype == CONV_DTYPE_BF16) {

@@ -55,7 +55,7 @@ struct SplitConfig {
   int ni;       // staging items per thread, at most
   int ns;       // MFMA steps per chunk and wave group
   int one;      // one chunk only
-  int occ;      // waves per SIMD it is compiled for
+  int occ;      // waves per SIMD it is declared for (its registers may allow more)
   int threads() const { return nwk * nwp * nwc * 64; }
 };
 const SplitConfig* split_configs(int* count);

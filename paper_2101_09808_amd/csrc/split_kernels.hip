@@ -15,7 +15,9 @@
 // one (3.1e-7), 1.4e-7 on a 1x1 layer of 1024 channels (4.0e-7).  An MFMA
 // rounds once for 32 products where the fp32 one rounds every four, and the
 // five small products have accumulators of their own (in one set of
-// accumulators they would round it six times per step: 3.6e-7 on C512).
+// accumulators they would round it six times per step: 3.6e-7 on C512).  Only
+// the image instances of two steps share one set: 7.6e-8 on a 3x3 stride 2 C3
+// K64 194x194 layer (fp32 MFMA kernel: 9.6e-8).
 //
 // bf16 inputs run the same kernels with one part per operand.
 //
@@ -23,19 +25,23 @@
 // reads as one contiguous kilobyte; the other is staged into LDS channel-
 // octet-fastest, [octet][pixel] of 16 bytes, so that every tap (r, s) of an
 // output pixel is another 16-byte slot: no im2col copy, any stride and
-// padding, and conflict-free reads.  Measured (back to back, In from HBM),
+// padding, and neighbouring lanes read neighbouring slots (LDS conflict cycles
+// are 10% to 15% of a kernel's cycles on the 3x3 layers, 26% on the 3x3 C512
+// one).  Measured (back to back through the Python calls),
 // before (fp32 MFMA kernels, or the transposed-tile bf16 kernel with its
 // phase-split pass) and after:
-//   3x3 C128 K128 30^2 N32            77.6 -> 40.1 us (184 TFLOP/s)
-//   3x3 C512 K512 9^2 N32             76.5 -> 51.5 us
-//   3x3 stride 2 C64 K128 56^2 N32    63.4 -> 32.2 us
-//   7x7 stride 2 C3 K64 224^2 N32     118  -> 72 us
-//   3x3 C512 K1024 17^2 N1            48.1 -> 41.5 us
-//   1x1 C1024 K28269 17^2 N1          283  -> 105 us
-//   bf16 3x3 C128 K128 28^2 N32       67.0 -> 18.3 us
-// What bounds it: on random data the bf16 MFMAs sustain 1.75-2.0 PFLOP/s (the
-// clock falls to 1.9 GHz), and per-workgroup timestamps show the vector-memory
-// instructions of a CU (about 17 cycles each) adding to the MFMA time.
+//   3x3 C128 K128 30^2 N32            78.1 -> 40.9 us (181 TFLOP/s)
+//   3x3 C512 K512 9^2 N32             76.8 -> 53.9 us
+//   3x3 stride 2 C64 K128 56^2 N32    63.7 -> 31.8 us
+//   7x7 stride 2 C3 K64 224^2 N32     118  -> 68.7 us
+//   3x3 C512 K1024 17^2 N1            48.4 -> 41.6 us
+//   1x1 C1024 K28269 17^2 N1          285  -> 112 us
+//   bf16 3x3 C128 K128 28^2 N32       67.0 -> 17.9 us
+// What bounds it (counters): the clock is 1.8 to 2.1 GHz; the MFMA pipes are
+// busy for 42% to 63% of a fp32 kernel's cycles on the CUs in use, and what they leave, less
+// about 8 k cycles for set-up, first loads and last stores, is 11 to 17 cycles
+// per vector-memory instruction of the CU (26 on the 1x1 layer, whose second
+// round of workgroups leaves CUs idle).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -135,9 +135,13 @@ namespace {
 // Estimated time in us.  Per-workgroup timestamps on MI355X (3x3 layers of
 // 128 and 512 channels, 512 -> 1024 at batch 1): a chunk takes the MFMA time
 // of its SIMD plus the time of the CU's vector-memory instructions, 17 cycles
-// each (within one workgroup they hardly overlap); set-up, first loads and the last stores take
-// 4-5 us per workgroup; the packing and the second launch 5 us plus the
-// packing's traffic.
+// each (within one workgroup they hardly overlap; counters give 11 to 17);
+// set-up, first loads and the last stores take 4-5 us per workgroup; the
+// packing and the second launch 5 us plus the packing's traffic.  Workgroups
+// per CU come from the waves per SIMD that an instance is declared for; the
+// bf16 instances of eight waves are declared for one workgroup and have the
+// registers for two (110 to 126), so their estimates are high where the tiles
+// exceed the CUs (1x1 C16 K752 43x31 at batch 19: 40 us, measured 31).
 double split_estimate(const SplitShape& s, const SplitPlan& p) {
   const SplitConfig& c = *p.cfg;
   const SplitGeom& g = p.g;
