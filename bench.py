@@ -59,6 +59,14 @@ def flops(c):
     return 2.0 * c.N * c.K * c.P * c.Q * c.C * c.R * c.S
 
 
+def mfma_peak(dtype, split):
+    """TFLOP/s that the kernels of a layer can reach on the matrix cores: fp32
+    on the split-operand kernels spends six bf16 products on each of its own."""
+    if dtype == "bf16":
+        return PEAK["bf16_mfma_tflops"]
+    return PEAK["bf16_mfma_tflops"] / 6 if split else PEAK["fp32_mfma_tflops"]
+
+
 def alg_bytes(c):
     e = 2 if c.dtype == "bf16" else 4
     return (c.N * c.C * c.H * c.W + c.K * c.C * c.R * c.S) * e + c.N * c.K * c.P * c.Q * 4
@@ -985,13 +993,17 @@ def table1_sweep():
         inner = B.conv_fwd_ex_inner_shape(*c.key(), c.stride, c.pad)
         plan, direct = B.conv_fwd_ex_plan(*c.key(), c.stride, c.pad)
         F, Bt = flops(c), alg_bytes(c)
-        t_mfma, t_hbm = F / (PEAK["fp32_mfma_tflops"] * 1e12), Bt / (PEAK["hbm_gbs"] * 1e9)
+        split = B.conv_fwd_split_plan(*c.key(), c.stride, c.pad)
+        peak = mfma_peak("f32", split)
+        t_mfma, t_hbm = F / (peak * 1e12), Bt / (PEAK["hbm_gbs"] * 1e9)
         bound = "mfma" if t_mfma >= t_hbm else "hbm"
         rows[c.name] = {
             "K": c.K, "C": c.C, "HW": c.H, "RS": c.R, "stride": c.stride, "pad": c.pad,
             "inner_shape": list(inner[:7]), "variant": plan["variant"], "split_c": plan["split_c"],
             "direct": direct, "pred_us": plan["pred_total_us"], "kernel_us": lk * 1e6, "gflops": F / lk / 1e9,
-            "pct_fp32_mfma_peak": 100 * F / lk / 1e12 / PEAK["fp32_mfma_tflops"],
+            # the split-operand instance that runs instead of the plan, if one does
+            "split_operand": split["id"] if split else None,
+            "mfma_peak_tflops": peak, "pct_mfma_peak": 100 * F / lk / 1e12 / peak,
             "alg_hbm_gbs": Bt / lk / 1e9, "pct_hbm_peak": 100 * Bt / lk / 1e9 / PEAK["hbm_gbs"],
             "bound": bound, "roofline_frac": max(t_mfma, t_hbm) / lk,
         }
@@ -1005,20 +1017,24 @@ def table1_report(rows):
              "strided or padded layers are rewritten as a stride-1 valid convolution (inner shape "
              "C', H', R') and run with the selector's plan, which reads the caller's In through the phase "
              "mapping where its kernel can (plan marked d) and otherwise runs on a phase-split or padded "
-             "copy of In.  Time = mean of 30 launches queued behind a "
+             "copy of In.  Layers marked s<i> run on instance i of the split-operand kernels instead (6 bf16 "
+             "products per fp32 one: peak 419.4 TFLOP/s).  Time = mean of 30 launches queued behind a "
              "spin kernel on rotating buffer sets, from HIP events.  Roofline fraction = time at the "
-             "layer's bound (fp32 MFMA 157.3 TFLOP/s or HBM 8 TB/s) over the measured time.  The "
+             "layer's bound (its kernels' MFMA peak, 157.3 TFLOP/s on the fp32 plans, or HBM 8 TB/s) over the measured time.  The "
              "depth-wise MobileNet layers are not Eq. (1).", "",
              "Command: `python bench.py --table1`", "",
-             "| layer | K | C | H=W | R=S | stride | inner (C', H', R') | plan | us | GFLOP/s | % fp32 peak "
+             "| layer | K | C | H=W | R=S | stride | inner (C', H', R') | plan | us | GFLOP/s | % MFMA peak "
              "| GB/s | bound | roofline frac |",
              "|---|---|---|---|---|---|---|---|---|---|---|---|---|"]
     for name, r in rows.items():
         ic = r["inner_shape"]
+        plan = f"v{r['variant']}/{r['split_c']}{' d' if r.get('direct') else ''}"
+        if r["split_operand"]:
+            plan = f"s{r['split_operand']}"
         lines.append(f"| {name.split('_', 1)[1]} | {r['K']} | {r['C']} | {r['HW']} | {r['RS']} | {r['stride']} | "
-                     f"({ic[1]}, {ic[3]}, {ic[5]}) | v{r['variant']}/{r['split_c']}{' d' if r.get('direct') else ''} | "
+                     f"({ic[1]}, {ic[3]}, {ic[5]}) | {plan} | "
                      f"{r['kernel_us']:.1f} | "
-                     f"{r['gflops']:.0f} | {r['pct_fp32_mfma_peak']:.1f} | {r['alg_hbm_gbs']:.0f} | {r['bound']} | "
+                     f"{r['gflops']:.0f} | {r['pct_mfma_peak']:.1f} | {r['alg_hbm_gbs']:.0f} | {r['bound']} | "
                      f"{r['roofline_frac']:.3f} |")
     return "\n".join(lines) + "\n"
 
@@ -1271,11 +1287,12 @@ def main():
         cold5 = summary(lr5.cold_runs(flush))
         del lr5
         ab = alg_bytes(c5) - c5.N * c5.K * c5.P * c5.Q * 2
+        split5 = B.conv_fwd_split_plan(*c5.key(), dtype=B.CONV_DTYPE_BF16)
         bf16out_row = {
             "dtype": "bf16", "out_dtype": "bf16", "variant": B.conv_fwd_bf16_out_plan(*c5.key())["variant"],
             "split_c": 1, "kernel_us": lk * 1e6, "gflops": flops(c5) / lk / 1e9,
-            "pct_fp32_mfma_peak": 100 * flops(c5) / lk / 1e12 / PEAK["fp32_mfma_tflops"],
-            "pct_dtype_mfma_peak": 100 * flops(c5) / lk / 1e12 / PEAK["bf16_mfma_tflops"],
+            "split_operand": split5["id"] if split5 else None, "mfma_peak_tflops": PEAK["bf16_mfma_tflops"],
+            "pct_mfma_peak": 100 * flops(c5) / lk / 1e12 / PEAK["bf16_mfma_tflops"],
             "alg_hbm_gbs": ab / lk / 1e9, "pct_hbm_peak": 100 * ab / lk / 1e9 / PEAK["hbm_gbs"],
             "cold": cold5,
         }
@@ -1291,22 +1308,21 @@ def main():
             lcold = summary(lrun.cold_runs(flush))
             del lrun
             lk = lr["mean_kernel_ms"] * 1e-3
-            lpeak = PEAK["bf16_mfma_tflops"] if lc.dtype == "bf16" else PEAK["fp32_mfma_tflops"]
             lplan = B.conv_fwd_plan(*lc.key(), dtype=B.CONV_DTYPE_BF16 if lc.dtype == "bf16" else B.CONV_DTYPE_F32)
             lsplit = B.conv_fwd_split_plan(*lc.key(), dtype=B.CONV_DTYPE_BF16 if lc.dtype == "bf16" else B.CONV_DTYPE_F32)
+            lpeak = mfma_peak(lc.dtype, lsplit)
             layers[lc.name] = {
                 "dtype": lc.dtype, "variant": lplan["variant"], "split_c": lplan["split_c"],
                 "num_wg": lplan["num_wg"],
                 # the split-operand instance that runs instead of the plan, if one does
                 "split_operand": lsplit["id"] if lsplit else None,
                 "kernel_us": lk * 1e6, "gflops": flops(lc) / lk / 1e9,
-                "pct_fp32_mfma_peak": 100 * flops(lc) / lk / 1e12 / PEAK["fp32_mfma_tflops"],
-                "pct_dtype_mfma_peak": 100 * flops(lc) / lk / 1e12 / lpeak,
+                # (of the peak of the kernels that run, mfma_peak)
+                "mfma_peak_tflops": lpeak, "pct_mfma_peak": 100 * flops(lc) / lk / 1e12 / lpeak,
                 "alg_hbm_gbs": alg_bytes(lc) / lk / 1e9,
                 "pct_hbm_peak": 100 * alg_bytes(lc) / lk / 1e9 / PEAK["hbm_gbs"],
                 "cold": lcold,
-                "cold_pct_fp32_mfma_peak_at_mean": 100 * flops(lc) / (lcold["mean_us"] * 1e-6) / 1e12
-                / PEAK["fp32_mfma_tflops"],
+                "cold_pct_mfma_peak_at_mean": 100 * flops(lc) / (lcold["mean_us"] * 1e-6) / 1e12 / lpeak,
                 "traffic": None if lsplit else counters.get((lc.name, plan_kernel_hash(lc, lplan))),
             }
             if not args.no_cpu:
@@ -1316,8 +1332,12 @@ def main():
             In_t, Ker_t = make_inputs(lc)
             _, tplan, _ = B.conv_fwd_tune(In_t.cuda(), Ker_t.cuda(), top_n=5, reps=5)
             del In_t, Ker_t
+            # (what runs after tuning: the split-operand kernels where they beat the tuned plan)
+            tsplit = B.conv_fwd_split_plan(*lc.key(), dtype=B.CONV_DTYPE_BF16 if lc.dtype == "bf16" else B.CONV_DTYPE_F32)
             tk = time_layer(lc, 50, 5, queued=True)["mean_kernel_ms"] * 1e-3
-            layers[lc.name].update({"mopt5_variant": tplan["variant"], "mopt5_split_c": tplan["split_c"],
+            layers[lc.name].update({"mopt5_split_operand": tsplit["id"] if tsplit else None,
+                                    "mopt5_variant": None if tsplit else tplan["variant"],
+                                    "mopt5_split_c": None if tsplit else tplan["split_c"],
                                     "mopt5_kernel_us": tk * 1e6, "mopt5_gflops": flops(lc) / tk / 1e9,
                                     "mopt5_pct_hbm_peak": 100 * alg_bytes(lc) / tk / 1e9 / PEAK["hbm_gbs"]})
             progress(f"layer {lc.name}: {lk * 1e6:.1f} us (MOpt-5 {tk * 1e6:.1f} us)")
@@ -1341,7 +1361,8 @@ def main():
                 "variant": lplan["variant"], "split_c": lplan["split_c"], "direct": ldirect,
                 "kernel_us": lk * 1e6,
                 "gflops": flops(lc) / lk / 1e9,
-                "pct_fp32_mfma_peak": 100 * flops(lc) / lk / 1e12 / PEAK["fp32_mfma_tflops"],
+                "mfma_peak_tflops": mfma_peak("f32", lsplit),
+                "pct_mfma_peak": 100 * flops(lc) / lk / 1e12 / mfma_peak("f32", lsplit),
                 "alg_hbm_gbs": alg_bytes(lc) / lk / 1e9,
                 "pct_hbm_peak": 100 * alg_bytes(lc) / lk / 1e9 / PEAK["hbm_gbs"],
                 "cold": lcold,
