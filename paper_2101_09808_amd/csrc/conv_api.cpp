@@ -407,10 +407,10 @@ int planned_time(const SplitShape& s, double* us) {
     // (the transposing bf16 kernel's ranking times were taken between events:
     // 73 us for the 226x226 layer that runs in 59-70 us, 16.0 us for a
     // 166x106 one that runs in 12.3 us.  Of 61 wide layers of up to 32 channels
-    // 8 keep their plans with this: five ran faster there, by 4% to 27%, and
+    // 8 keep their plans with this: five ran faster there, by 2% to 27%, and
     // three, 163x172 at batch 2, 163x144 at batch 8 and 128x96 at batch 4, would
     // have been 1.4 to 1.7 times as fast on the split kernels.  bf16 Out of the
-    // 226x226 layer too: 63.9 against 56.9 us, with fp32 Out 59.6 against 65.9.)
+    // 226x226 layer too: 63.5 against 58.0 us, with fp32 Out 59.6 against 65.0.)
     if (st == CONV_OK) *t = e.plan.rank_us * (e.v->family == FAMILY_BF16_TR ? 0.7 : 1.0) + extra;
     return st;
   };
